@@ -493,7 +493,7 @@ fbl_status fbl_proj(uint32_t op, int64_t M, int64_t K, int64_t N, const void* a,
  * fbl_proj (the projection products of section 2.2's LoRA example) for either
  * storage type: dtype FBL_BF16 is fbl_proj exactly;
  * FBL_F32 runs the same three products on fp32 operands and result (fp32
- * MFMAs, fp32 accumulation) with one tile shape -- tile must be
+ * MFMAs, fp32 accumulation) with a tile of its own choice -- tile must be
  * FBL_GEMM_TILE_AUTO (else FBL_ERR_ARG) -- any extents and leading
  * dimensions, and 4-byte (natural) alignment; the other checks are
  * fbl_proj's.  FBL_ERR_DTYPE for another dtype.

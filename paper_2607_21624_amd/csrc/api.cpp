@@ -877,8 +877,8 @@ void proj_shape(uint32_t op, int64_t M, int64_t K, int64_t N, ProjPlan& pl) {
 
 // es: element size (2: bf16, 4: fp32).  bf16 operands are staged by 16-byte
 // DMA loads (16-byte aligned pointers and rows, output widths a multiple of
-// 4, contraction a multiple of 8); fp32 operands by bounds-checked element
-// loads (natural alignment only).
+// 4, contraction a multiple of 8); fp32 operands through registers by
+// range-checked loads (natural alignment only).
 fbl_status proj_plan(uint32_t op, int64_t M, int64_t K, int64_t N, const void* a, int64_t lda, const void* b,
                      int64_t ldb, void* c, int64_t ldc, ProjPlan& pl, int es = 2) {
     if (op > FBL_PROJ_BWD_WEIGHT) return FBL_ERR_ARG;
@@ -921,7 +921,8 @@ fbl_status proj_plan(uint32_t op, int64_t M, int64_t K, int64_t N, const void* a
     // odd row width) would lose the operand's last element: the load spans
     // end at the 16-byte chunk holding it.  Pointers and row strides are
     // 16-byte aligned, so that chunk is aligned and never crosses a page.
-    const auto chunk_end = [](int64_t n) { return (uint32_t)((n + 15) / 16 * 16); };
+    // fp32 operands (4-byte aligned) end where their last element does.
+    const auto chunk_end = [es](int64_t n) { return (uint32_t)(es == 2 ? (n + 15) / 16 * 16 : n); };
     p.a_bytes = chunk_end(sa);
     p.b_bytes = chunk_end(sb);
     p.c_bytes = (uint32_t)sc;  // stores are 4 elements wide and output widths a multiple of 4
@@ -1065,7 +1066,7 @@ fbl_status fbl_proj_dt(uint32_t op, int32_t dtype, int64_t M, int64_t K, int64_t
     ProjPlan pl;
     const fbl_status st = proj_plan(op, M, K, N, a, lda, b, ldb, c, ldc, pl, dtype == FBL_BF16 ? 2 : 4);
     if (st != FBL_OK) return st;
-    if (dtype == FBL_F32) {  // one tile shape (64 x 64 outputs, 16-deep steps)
+    if (dtype == FBL_F32) {  // its tile follows from the shape
         if (tile != FBL_GEMM_TILE_AUTO) return FBL_ERR_ARG;
         const hipError_t e = fbl::launch_proj_gemm_f32(pl.a_kmajor, pl.b_nmajor, pl.p, static_cast<hipStream_t>(stream));
         return e == hipSuccess ? FBL_OK : FBL_ERR_HIP;

@@ -252,6 +252,39 @@ def test_proj_fp32_matches_oracle(M, K, N):
         assert rel_err(to_np(view), ref) <= 1e-4, f"op {op}"
 
 
+@pytest.mark.parametrize("M,K,N", [(4000, 24, 2040), (2100, 20, 4100), (1290, 52, 2050), (1020, 33, 1000),
+                                   (129, 70, 333), (45, 803, 77), (1, 769, 1)])
+def test_proj_fp32_every_tile(M, K, N):
+    """Each fp32 tile (128x128 ... 32x32, the contraction split over 1, 2, 4 and
+    8 wavefronts) on ragged extents: operands are column views of wider buffers
+    at an odd 4-byte offset whose other columns and following rows are NaN, so a
+    read past an extent that reaches a result shows.  Each result is within the
+    bound of a K-term fp32 sum in any order, (K + 2) 2^-24 sum |a||b|."""
+    import torch
+    fbl = _lib()
+    rng = np.random.default_rng(M + 5 * K + 11 * N)
+
+    def wide(x):
+        buf = torch.full((x.shape[0] + 1, x.shape[1] + 6), float("nan"), dtype=torch.float32, device="cuda")
+        view = buf[:x.shape[0], 1:1 + x.shape[1]]
+        view.copy_(torch.from_numpy(x))
+        return view
+
+    x, w, dy = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
+    X, W, dY = wide(x), wide(w), wide(dy)
+    note(f"proj fp32 tiles M={M} K={K} N={N}")
+    for op, a, b, fa, fb in ((fbl.FBL_PROJ_FWD, X, W, x, w), (fbl.FBL_PROJ_BWD_DATA, dY, W, dy, w.T),
+                             (fbl.FBL_PROJ_BWD_WEIGHT, X, dY, x.T, dy)):
+        ref = fa.astype(np.float64) @ fb.astype(np.float64)
+        bound = (fa.shape[1] + 2) * 2.0 ** -24 * (np.abs(fa).astype(np.float64) @ np.abs(fb).astype(np.float64))
+        out = torch.full((ref.shape[0] + 1, ref.shape[1] + 3), float("nan"), dtype=torch.float32, device="cuda")
+        view = out[:ref.shape[0], :ref.shape[1]]
+        fbl.proj(op, a, b, out=view)
+        torch.cuda.synchronize()
+        assert torch.isnan(out[ref.shape[0]:]).all() and torch.isnan(out[:, ref.shape[1]:]).all(), f"op {op}: outside"
+        assert (np.abs(to_np(view) - ref) <= bound).all(), f"op {op}"
+
+
 @pytest.mark.parametrize("op,M,K,N", [(0, 512, 2048, 8192), (1, 512, 4096, 12288), (2, 512, 1024, 4096),
                                       (0, 1024, 512, 4096), (1, 300, 1000, 2048)])
 def test_auto_tile_query_matches_dispatch(op, M, K, N):
