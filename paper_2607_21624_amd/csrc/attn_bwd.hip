@@ -8,26 +8,14 @@
 //   P    = exp(scale q_i.k_j - LSE_i)          (recomputed from the saved LSE)
 //   dP   = dO V^T,  dS = P (dP - D)
 //   dV   = P^T dO,  dK = scale dS^T Q,  dQ = scale dS K
-// Three launches, no atomics, every output written once:
+// This file holds two of the backward's kernels, for both storage types, and
+// the launch of its passes:
 //   attn_bwd_stats  per query row: LSE*log2(e) (+inf for an empty row) and D.
-//   attn_bwd_kv     key/value-major.  A workgroup owns 128 keys of one
-//                   (batch, kv head); each wavefront keeps its 32 K and V rows
-//                   and its dK^T, dV^T accumulators in registers and walks the
-//                   query blocks of every query head of its GQA group.  The
-//                   reductions over queries that build dK/dV (the M direction
-//                   of section 4.2's naming) and the group sum over
-//                   the G query heads never leave registers.
-//   attn_bwd_q      query-major.  A workgroup owns 128 queries of one
-//                   (batch, query head) and walks the key tiles, recomputing S
-//                   and dP, and accumulates dQ^T in registers (the N
-//                   direction).
-// Recomputing S and dP in the query-major pass costs two extra products per
-// (query, key) pair; it replaces fp32 atomics, which run at ~1.3 TB/s on this
-// part -- far slower than the 3 products they would save at these shapes.
-// Q/dO (kv pass) and K/V (q pass) tiles are staged once per block in LDS by
-// DMA and serve both reduction directions (tile invariance, section 4.2): row
-// reads where the contraction runs along d, transposed reads
-// (ds_read_b64_tr_b16) where it runs along tokens.
+//   attn_bwd_fused  the whole backward in one launch, up to 128 keys.
+// The kv and dQ passes are attn_bwd_kv.hip, attn_bwd_dq.hip and attn_bwd_q.hip
+// (bf16) and attn_f32.hip (fp32).  No atomics: fp32 atomics run at ~1.3 TB/s on
+// this part, far slower than the products they would save; every output is
+// written once.
 #include <type_traits>
 
 #include "cdna4.hpp"
@@ -40,9 +28,7 @@ namespace fbl {
 namespace {
 
 constexpr int kWaves = 4;
-constexpr int kKvBN = 32 * kWaves;  // keys per kv-pass workgroup
-constexpr int kQBM = 32 * kWaves;   // queries per q-pass workgroup
-constexpr int kQBN = 64;            // keys per q-pass tile
+constexpr int kKvBN = 32 * kWaves;  // keys per workgroup of the one-launch backward
 
 // ------------------------------------------------------------------ stats
 // A workgroup covers kStatRows consecutive query tokens of one (batch, query
@@ -104,14 +90,17 @@ __global__ __launch_bounds__(256) void attn_bwd_stats(BwdArgs a) {
     }
 }
 
-// ------------------------------------------------------------- kv pass
-// FUSED: the whole backward in this one pass, for key/value sequences of at
-// most one key block (kKvBN keys): every workgroup then holds all the keys of
-// its (batch, kv head), so it also forms each query block's row statistics
-// (D from O and dO, LSE from the forward's output) and its dQ = scale dS K
-// completely -- no statistics pass, no stored dS, no dQ pass.
-template <typename T, int D, bool FUSED>
-struct KvCfg {
+// ------------------------------------------------------ one-launch backward
+// The whole backward in one launch, for key/value sequences of at most kKvBN
+// keys.  A workgroup owns the keys of one (batch, kv head); each wavefront keeps
+// its 32 K and V rows and its dK^T, dV^T accumulators in registers and walks the
+// query blocks of every query head of its GQA group, whose Q and dO tiles are
+// staged once in LDS by DMA and serve both reduction directions (tile
+// invariance, section 4.2).  It also forms each block's row statistics (D from
+// O and dO, LSE from the forward's output) and its dQ = scale dS K completely --
+// no statistics pass, no stored dS, no dQ pass.
+template <typename T, int D>
+struct FusedCfg {
     static constexpr int BQ = D == 128 ? 32 : 64;  // queries per block (register budget)
     static constexpr int NQT = BQ / 32;
     static constexpr int TILE = BQ * D;             // elements of one Q or dO tile
@@ -119,28 +108,26 @@ struct KvCfg {
     // LDS: Q0 Q1 dO0 dO1 tiles, then lse2 0/1 and D 0/1 (256 bytes each: one
     // 64-lane dword DMA; the first BQ floats are used)
     static constexpr int OFF_STATS = 4 * TB;
-    // FUSED: the block of kKvBN K rows (the dQ product's operand, staged once)
+    // the block of kKvBN K rows (the dQ product's operand, staged once)
     // and one block of dS, [BQ queries][DS_PITCH] of T (rows padded by 8
     // elements: 16-byte aligned, and consecutive rows on other LDS banks)
     static constexpr int OFF_K = OFF_STATS + 4 * 256;
     static constexpr int KT_BYTES = kKvBN * D * (int)sizeof(T);
     static constexpr int DS_PITCH = kKvBN + 8;
     static constexpr int OFF_DS = OFF_K + KT_BYTES;
-    // FUSED with bf16 storage: the block's O rows too (staged with Q and dO, two
+    // bf16 storage: the block's O rows too (staged with Q and dO, two
     // buffers), so that D is formed from LDS; fp32 forms it from global memory
-    static constexpr bool O_TILE = FUSED && sizeof(T) == 2;
+    static constexpr bool O_TILE = sizeof(T) == 2;
     static constexpr int OFF_O = (OFF_DS + BQ * DS_PITCH * (int)sizeof(T) + 1023) / 1024 * 1024;
-    static constexpr int BYTES = !FUSED ? OFF_STATS + 4 * 256
-                                 : O_TILE ? OFF_O + 2 * TB
-                                          : OFF_DS + BQ * DS_PITCH * (int)sizeof(T);
+    static constexpr int BYTES = O_TILE ? OFF_O + 2 * TB : OFF_DS + BQ * DS_PITCH * (int)sizeof(T);
     static_assert(BYTES <= 160 * 1024, "LDS of one workgroup");
     static_assert(OFF_K % 1024 == 0, "the K block starts on a 1 KB boundary");
     static_assert(OFF_O % 1024 == 0 && TB % 1024 == 0, "the O tiles start on 1 KB boundaries");
 };
 
-template <typename T, int D, bool FUSED>
-__device__ __forceinline__ void kv_pass(const BwdArgs& a) {
-    using C = KvCfg<T, D, FUSED>;
+template <typename T, int D>
+__global__ __launch_bounds__(256, 1) void attn_bwd_fused(BwdArgs a) {
+    using C = FusedCfg<T, D>;
     constexpr int NC = D / 16;
     constexpr int ND = D / 32;
     constexpr int BQ = C::BQ;
@@ -155,16 +142,14 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
     const int g = lane >> 5;
     const int c32 = lane & 31;
     const int S = a.S, Skv = a.Skv;  // query tokens, key tokens
-    const int nkb = (Skv + kKvBN - 1) / kKvBN;
-    const int logical = xcd_logical_id(blockIdx.x, nkb * a.Hkv * a.B, gridDim.x);
+    const int logical = xcd_logical_id(blockIdx.x, a.Hkv * a.B, gridDim.x);
     if (logical < 0) return;
-    const int kblk = logical % nkb;
-    const int hk = (logical / nkb) % a.Hkv;
-    const int b = logical / (nkb * a.Hkv);
+    const int hk = logical % a.Hkv;
+    const int b = logical / a.Hkv;
     const int G_ = a.Hq / a.Hkv;
     int kv_end = Skv;
     if (a.mask.kv_len) kv_end = min(max(a.mask.kv_len[b], 0), Skv);
-    const int k0 = kblk * kKvBN;
+    constexpr int k0 = 0;  // one key block
     const int kw0 = k0 + wave * 32;  // first key of this wave
     const int key = kw0 + c32;       // this lane's key (column of S)
     const bool key_ok = key < kv_end;
@@ -224,7 +209,7 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
     const uint32_t qbytes = (uint32_t)(a.mq.ss * es), obytes = (uint32_t)(a.mdo.ss * es);
     const uint32_t qspan = (uint32_t)((int64_t)(S - 1) * a.mq.ss * es + D * es);
     const uint32_t ospan = (uint32_t)((int64_t)(S - 1) * a.mdo.ss * es + D * es);
-    DmaPlan<T, D, BQ, kWaves> pof;  // O rows (FUSED, bf16)
+    DmaPlan<T, D, BQ, kWaves> pof;  // O rows (bf16)
     const uint32_t ofbytes = (uint32_t)(a.mo.ss * es);
     const uint32_t ofspan = (uint32_t)((int64_t)(S - 1) * a.mo.ss * es + D * es);
     if constexpr (C::O_TILE) pof.init(ofbytes, wave, lane);
@@ -241,18 +226,13 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
             const Rsrc rof = make_rsrc(static_cast<const T*>(a.o) + a.mo.head_base(b, h), ofspan);
             pof.issue(lds + C::OFF_O + buf * TB, rof, (uint32_t)q0 * ofbytes, wave);
         }
-        if constexpr (FUSED) {  // wave 0: the forward's LSE of the block's queries (D is formed in the step)
-            if (wave == 0) {
-                const float* row = a.lse + ((int64_t)b * a.Hq + h) * S;
-                dma4(make_rsrc(row, (uint32_t)(S * 4)), lds + C::OFF_STATS + buf * 256, (uint32_t)lane * 4u,
-                     (uint32_t)q0 * 4u);
-            }
-        } else if (wave < 2) {  // wave 0: lse2 of the block's queries, wave 1: D
-            const float* row = a.stats + (2 * ((int64_t)b * a.Hq + h) + wave) * S;
-            dma4(make_rsrc(row, (uint32_t)(S * 4)), lds + C::OFF_STATS + (2 * wave + buf) * 256, (uint32_t)lane * 4u, (uint32_t)q0 * 4u);
+        if (wave == 0) {  // the forward's LSE of the block's queries (D is formed in the step)
+            const float* row = a.lse + ((int64_t)b * a.Hq + h) * S;
+            dma4(make_rsrc(row, (uint32_t)(S * 4)), lds + C::OFF_STATS + buf * 256, (uint32_t)lane * 4u,
+                 (uint32_t)q0 * 4u);
         }
     };
-    // FUSED: D_i = sum_k dO_ik O_ik of the block's BQ rows of query head h,
+    // D_i = sum_k dO_ik O_ik of the block's BQ rows of query head h,
     // TPR threads per row, into the block's D slot
     auto form_d = [&](int buf, int h, int q0) {
         constexpr int EPC = 16 / (int)sizeof(T);
@@ -330,10 +310,9 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 f32x4 l4 = *(const FBL_LDS f32x4*)(uintptr_t)(st_addr + (qt * 32 + 8 * rr) * 4);
-                if constexpr (FUSED) {  // the forward's natural-log LSE: to log2 units, +inf for an empty row
+                // the forward's natural-log LSE: to log2 units, +inf for an empty row
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) l4[j] = l4[j] == -INFINITY ? INFINITY : l4[j] * kLog2e;
-                }
+                for (int j = 0; j < 4; ++j) l4[j] = l4[j] == -INFINITY ? INFINITY : l4[j] * kLog2e;
                 const f32x4 d4 = *(const FBL_LDS f32x4*)(uintptr_t)(st_addr + 512 + (qt * 32 + 8 * rr) * 4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -381,24 +360,23 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
                 }
             }
         }
-        if constexpr (FUSED) {  // dS of the wave's 32 keys into the block's dS rows: [query][key]
-            T* sds = reinterpret_cast<T*>(kv_smem + C::OFF_DS);
+        // dS of the wave's 32 keys into the block's dS rows: [query][key]
+        T* sds = reinterpret_cast<T*>(kv_smem + C::OFF_DS);
 #pragma unroll
-            for (int qt = 0; qt < NQT; ++qt)
+        for (int qt = 0; qt < NQT; ++qt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) store_out(sds + (qt * 32 + acc_row(r, g)) * C::DS_PITCH + key - k0, dp[qt][r]);
-        }
+            for (int r = 0; r < 16; ++r) store_out(sds + (qt * 32 + acc_row(r, g)) * C::DS_PITCH + key - k0, dp[qt][r]);
     };
-    // FUSED: dQ of the block, dQ^T(d x queries) = scale K^T dS^T over the
+    // dQ of the block, dQ^T(d x queries) = scale K^T dS^T over the
     // workgroup's kKvBN keys -- A = K^T from the K block (transposed reads),
     // B = dS^T from the dS rows (row reads); NQT x ND output tiles spread over
     // the four wavefronts; query row q of head h at q0 + 32qt + lane % 32
-    // FUSED: dQ of a block is computed after its dS and (bf16) stored at the
+    // dQ of a block is computed after its dS and (bf16) stored at the
     // start of the next step, after that step's wait: its stores then have a
     // whole step to retire before the next wait (which covers every
     // outstanding memory operation of the wavefront).  One output tile per
     // wavefront.
-    static_assert(!FUSED || NQT * ND <= kWaves, "at most one dQ tile per wavefront");
+    static_assert(NQT * ND <= kWaves, "at most one dQ tile per wavefront");
     f32x16 dq_acc = f32x16{};
     int dq_h = -1, dq_q0 = 0;  // the block whose dQ tile is held (dq_h < 0: none)
     auto dq_flush_now = [&]() {
@@ -456,25 +434,21 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
         if (it + 1 < n_iter) issue(it + 1);
         const int q0 = (qb_start + it % per_head) * BQ;
         const int h = hk * G_ + it / per_head;
-        if constexpr (FUSED) {
-            if constexpr (kBf16) dq_flush_now();  // the previous block's dQ tile
-            form_d(buf, h, q0);
-            __syncthreads();  // the block's D row is in LDS
-        }
+        if constexpr (kBf16) dq_flush_now();  // the previous block's dQ tile
+        form_d(buf, h, q0);
+        __syncthreads();  // the block's D row is in LDS
         // a wave whose keys all follow every query of the block has nothing to add
         if (!(a.mask.causal && q0 + BQ - 1 < kw0) && kw0 < kv_end) {
             compute(mask_c, buf, q0);
-        } else if constexpr (FUSED) {  // its dS columns are zero
+        } else {  // its dS columns are zero
             T* sds = reinterpret_cast<T*>(kv_smem + C::OFF_DS);
 #pragma unroll
             for (int qt = 0; qt < NQT; ++qt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) store_out(sds + (qt * 32 + acc_row(r, g)) * C::DS_PITCH + key - k0, 0.f);
         }
-        if constexpr (FUSED) {
-            __syncthreads();  // every wavefront's dS columns are in LDS
-            dq_block(h, q0);
-        }
+        __syncthreads();  // every wavefront's dS columns are in LDS
+        dq_block(h, q0);
         if constexpr (kBf16) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) lo.row[c] += flip;
@@ -488,20 +462,16 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
         flip = -flip;
     };
 
-    if constexpr (FUSED) {  // the workgroup's K rows for the dQ products (rows past S_kv read as zeros)
-        DmaPlan<T, D, kKvBN, kWaves> pk;
-        pk.init((uint32_t)(a.mk.ss * es), wave, lane);
-        pk.issue(lds + C::OFF_K, make_rsrc(kbase, (uint32_t)((int64_t)(Skv - 1) * a.mk.ss * es + D * es)), 0u, wave);
-    }
-    if constexpr (FUSED) {  // no allowed key (kv_len = 0): dQ of the whole group is zero
-        if (n_iter == 0) {
-            for (int64_t i = threadIdx.x; i < (int64_t)G_ * S * (D / 4); i += 256) {
-                const int c4 = (int)(i % (D / 4));
-                const int sq = (int)((i / (D / 4)) % S);
-                const int h = hk * G_ + (int)(i / ((int64_t)S * (D / 4)));
-                store4(static_cast<T*>(a.dq) + a.mdq.head_base(b, h) + (int64_t)sq * a.mdq.ss + 4 * c4, 0.f, 0.f, 0.f,
-                       0.f);
-            }
+    // the workgroup's K rows for the dQ products (rows past S_kv read as zeros)
+    DmaPlan<T, D, kKvBN, kWaves> pk;
+    pk.init((uint32_t)(a.mk.ss * es), wave, lane);
+    pk.issue(lds + C::OFF_K, make_rsrc(kbase, (uint32_t)((int64_t)(Skv - 1) * a.mk.ss * es + D * es)), 0u, wave);
+    if (n_iter == 0) {  // no allowed key (kv_len = 0): dQ of the whole group is zero
+        for (int64_t i = threadIdx.x; i < (int64_t)G_ * S * (D / 4); i += 256) {
+            const int c4 = (int)(i % (D / 4));
+            const int sq = (int)((i / (D / 4)) % S);
+            const int h = hk * G_ + (int)(i / ((int64_t)S * (D / 4)));
+            store4(static_cast<T*>(a.dq) + a.mdq.head_base(b, h) + (int64_t)sq * a.mdq.ss + 4 * c4, 0.f, 0.f, 0.f, 0.f);
         }
     }
     if (n_iter > 0) issue(0);
@@ -510,7 +480,7 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
         for (int j = 0; j < n_mask; ++j, ++it) step(std::true_type{}, it);
         for (int j = n_mask; j < per_head; ++j, ++it) step(std::false_type{}, it);
     }
-    if constexpr (FUSED && kBf16) dq_flush_now();
+    if constexpr (kBf16) dq_flush_now();
 
     // dK (times scale) and dV rows of this wave's keys: lane <-> key, 4 consecutive d per store
     if (key < Skv) {
@@ -529,249 +499,13 @@ __device__ __forceinline__ void kv_pass(const BwdArgs& a) {
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256, 1) void attn_bwd_kv(BwdArgs a) {
-    kv_pass<T, D, false>(a);
-}
-
-// the one-launch backward (keys within one block of kKvBN)
-template <typename T, int D>
-__global__ __launch_bounds__(256, 1) void attn_bwd_fused(BwdArgs a) {
-    kv_pass<T, D, true>(a);
-}
-
-// --------------------------------------------------------------- q pass
-template <typename T, int D>
-struct QSmem {
-    static constexpr int TILE = kQBN * D;
-    static constexpr int TB = TILE * (int)sizeof(T);
-    static constexpr int BYTES = 4 * TB;  // K0 K1 V0 V1
-};
-
-template <typename T, int D>
-__global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void attn_bwd_q(BwdArgs a) {
-    constexpr int NC = D / 16;
-    constexpr int ND = D / 32;
-    constexpr int TILE = QSmem<T, D>::TILE;
-    constexpr int TB = QSmem<T, D>::TB;
-    constexpr bool kBf16 = sizeof(T) == 2;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char q_smem[];
-    T* smem = reinterpret_cast<T*>(q_smem);
-    const uint32_t lds = lds_addr(q_smem);  // LDS byte address of the tiles
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = lane >> 5;
-    const int c32 = lane & 31;
-    const int S = a.S;
-    const int nqb = (S + kQBM - 1) / kQBM;
-    const int logical = xcd_logical_id(blockIdx.x, nqb * a.Hq * a.B, gridDim.x);
-    if (logical < 0) return;
-    const int rank = logical % nqb;
-    const int h = (logical / nqb) % a.Hq;
-    const int b = logical / (nqb * a.Hq);
-    const int qb = a.mask.causal ? (nqb - 1 - rank) : rank;
-    const int hk = h / (a.Hq / a.Hkv);
-    const int Skv = a.Skv;  // key tokens
-    int kv_end = Skv;
-    if (a.mask.kv_len) kv_end = min(max(a.mask.kv_len[b], 0), Skv);
-    const int q0 = qb * kQBM;
-    const int qw0 = q0 + wave * 32;
-    const int qi = qw0 + c32;  // this lane's query (column of S^T)
-    int k_hi = kv_end;
-    if (a.mask.causal) k_hi = min(k_hi, q0 + kQBM);
-    const int nkb = (k_hi + kQBN - 1) / kQBN;
-
-    // Q^T and dO^T as B operands: lane <-> query, in-lane d = 16c + 8g + e
-    Frag<T> qf[NC], of[NC];
-    {
-        const T* qrow = static_cast<const T*>(a.q) + a.mq.head_base(b, h) + (int64_t)qi * a.mq.ss;
-        const T* orow = static_cast<const T*>(a.dout) + a.mdo.head_base(b, h) + (int64_t)qi * a.mdo.ss;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            pack_frag(qf[c], z);
-            pack_frag(of[c], z);
-            if (qi < S) {
-                if constexpr (kBf16) {
-                    qf[c].v = __builtin_bit_cast(bf16x8, load16(qrow + 16 * c + 8 * g));
-                    of[c].v = __builtin_bit_cast(bf16x8, load16(orow + 16 * c + 8 * g));
-                } else {
-                    const f32x4 q0v = __builtin_bit_cast(f32x4, load16(qrow + 16 * c + 8 * g));
-                    const f32x4 q1v = __builtin_bit_cast(f32x4, load16(qrow + 16 * c + 8 * g + 4));
-                    const f32x4 o0v = __builtin_bit_cast(f32x4, load16(orow + 16 * c + 8 * g));
-                    const f32x4 o1v = __builtin_bit_cast(f32x4, load16(orow + 16 * c + 8 * g + 4));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        qf[c].v[e] = q0v[e];
-                        qf[c].v[4 + e] = q1v[e];
-                        of[c].v[e] = o0v[e];
-                        of[c].v[4 + e] = o1v[e];
-                    }
-                }
-            }
-        }
-    }
-    float lse2 = INFINITY, drow = 0.f;  // this lane's query row statistics
-    if (qi < S) {
-        const int64_t bh = (int64_t)b * a.Hq + h;
-        lse2 = a.stats[2 * bh * S + qi];
-        drow = a.stats[(2 * bh + 1) * S + qi];
-    }
-
-    f32x16 dq[ND];  // dQ^T: rows = d (32t + acc_row), columns = queries (lane)
-#pragma unroll
-    for (int t = 0; t < ND; ++t) dq[t] = f32x16{};
-
-    const uint32_t es = sizeof(T);
-    const Rsrc rk = make_rsrc(static_cast<const T*>(a.k) + a.mk.head_base(b, hk),
-                              (uint32_t)((int64_t)(Skv - 1) * a.mk.ss * es + D * es));
-    const Rsrc rv = make_rsrc(static_cast<const T*>(a.v) + a.mv.head_base(b, hk),
-                              (uint32_t)((int64_t)(Skv - 1) * a.mv.ss * es + D * es));
-    const uint32_t kbytes = (uint32_t)(a.mk.ss * es), vbytes = (uint32_t)(a.mv.ss * es);
-    DmaPlan<T, D, kQBN, kWaves> pk, pv;
-    pk.init(kbytes, wave, lane);
-    pv.init(vbytes, wave, lane);
-    LaneOffsets<D> lo;
-    if constexpr (kBf16) lo.init(lds_addr(q_smem), lane);
-    int32_t flip = TB;
-
-    auto tile = [&](auto mask_c, int k0) {
-        constexpr bool MASK = decltype(mask_c)::value;
-        const int BUF = (k0 / kQBN) & 1;
-        // S^T = K Q^T and dP^T = V dO^T: lane <-> query, in-lane key kt*32 + acc_row
-        f32x16 s[2], dp[2];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            s[kt] = f32x16{};
-            dp[kt] = f32x16{};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                Frag<T> fk, fv;
-                if constexpr (kBf16) {
-                    fk.v = lds_b128(lo.row[c], kt * 32 * D * 2);
-                    fv.v = lds_b128(lo.row[c], 2 * TB + kt * 32 * D * 2);
-                } else {
-                    tile_row_frag<D>(fk, smem + BUF * TILE, kt * 32 + c32, 16 * c + 8 * g);
-                    tile_row_frag<D>(fv, smem + (2 + BUF) * TILE, kt * 32 + c32, 16 * c + 8 * g);
-                }
-                mma(s[kt], fk, qf[c]);
-                mma(dp[kt], fv, of[c]);
-            }
-        }
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                float p = fast_exp2(__builtin_fmaf(s[kt][r], a.scale_log2, -lse2));
-                if constexpr (MASK) {
-                    const int kk = k0 + kt * 32 + acc_row(r, g);
-                    if (kk >= kv_end || (a.mask.causal && kk > qi)) p = 0.f;
-                }
-                dp[kt][r] = p * (dp[kt][r] - drow);
-            }
-        }
-        // dQ^T += K^T dS^T over the 64 keys: chunk (kt, cc) covers keys
-        // kt*32 + 16cc + {4g..4g+3, 8+4g..8+4g+3} in accumulator order
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-            for (int cc = 0; cc < 2; ++cc) {
-                Frag<T> dsb;
-                float dsv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dsv[e] = dp[kt][8 * cc + e];
-                pack_frag(dsb, dsv);
-#pragma unroll
-                for (int t = 0; t < ND; ++t) {
-                    Frag<T> fk;
-                    if constexpr (kBf16) {
-                        const uint32_t rb = (kt * 32 + 16 * cc) * D * 2;
-                        const bf16x4 x0 = lds_tr(lo.tr[t][0], rb), x1 = lds_tr(lo.tr[t][1], rb);
-                        fk.v = bf16x8{x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-                    } else {
-                        const int row0 = kt * 32 + 16 * cc + 4 * g;
-                        tile_tr_frag<D>(fk, smem + BUF * TILE, row0, row0 + 8, 32 * t, lane);
-                    }
-                    mma(dq[t], fk, dsb);
-                }
-            }
-        }
-    };
-
-    auto step = [&](auto mask_c, int kb) {
-        const int k0 = kb * kQBN;
-        wait_vmcnt<0>();
-        __syncthreads();
-        if (kb + 1 < nkb) {
-            const uint32_t nb = (uint32_t)((kb + 1) & 1);
-            pk.issue(lds + nb * TB, rk, (uint32_t)(k0 + kQBN) * kbytes, wave);
-            pv.issue(lds + (2 + nb) * TB, rv, (uint32_t)(k0 + kQBN) * vbytes, wave);
-        }
-        tile(mask_c, k0);
-        if constexpr (kBf16) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) lo.row[c] += flip;
-#pragma unroll
-            for (int t = 0; t < ND; ++t) {
-                lo.tr[t][0] += flip;
-                lo.tr[t][1] += flip;
-            }
-        }
-        flip = -flip;
-    };
-
-    if (nkb > 0) {
-        pk.issue(lds, rk, 0u, wave);
-        pv.issue(lds + 2 * TB, rv, 0u, wave);
-    }
-    const int n_full = min(nkb, min(kv_end, a.mask.causal ? q0 + 1 : Skv) / kQBN);
-    for (int kb = 0; kb < n_full; ++kb) step(std::false_type{}, kb);
-    for (int kb = n_full; kb < nkb; ++kb) step(std::true_type{}, kb);
-
-    if (qi < S) {
-        T* dqrow = static_cast<T*>(a.dq) + a.mdq.head_base(b, h) + (int64_t)qi * a.mdq.ss;
-#pragma unroll
-        for (int t = 0; t < ND; ++t) {
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int dcol = 32 * t + 8 * rr + 4 * g;
-                store4(dqrow + dcol, dq[t][4 * rr] * a.scale, dq[t][4 * rr + 1] * a.scale, dq[t][4 * rr + 2] * a.scale,
-                       dq[t][4 * rr + 3] * a.scale);
-            }
-        }
-    }
-}
-
-// Explicit instantiations: the host-side launch stubs of every kernel used
-// below.  bf16 storage runs the software-pipelined passes of attn_bwd_kv.hip,
-// attn_bwd_dq.hip and attn_bwd_q.hip; the two passes here serve fp32.
-#define FBL_BWD_KERNELS_F32(D)                                     \
-    template __global__ void attn_bwd_stats<float, D>(BwdArgs);   \
-    template __global__ void attn_bwd_kv<float, D>(BwdArgs);        \
-    template __global__ void attn_bwd_q<float, D>(BwdArgs);
-FBL_BWD_KERNELS_F32(32)
-FBL_BWD_KERNELS_F32(64)
-FBL_BWD_KERNELS_F32(128)
-#undef FBL_BWD_KERNELS_F32
-template __global__ void attn_bwd_stats<bf16, 32>(BwdArgs);
-template __global__ void attn_bwd_stats<bf16, 64>(BwdArgs);
-template __global__ void attn_bwd_stats<bf16, 128>(BwdArgs);
-
-template <int D>
-hipError_t set_bwd_lds_f32() {
-    const hipError_t e = ensure_dynamic_lds<&attn_bwd_kv<float, D>>(KvCfg<float, D, false>::BYTES);
-    if (e != hipSuccess) return e;
-    return ensure_dynamic_lds<&attn_bwd_q<float, D>>(QSmem<float, D>::BYTES);
-}
-
 int padded8(int n) { return (n + 7) / 8 * 8; }
 
 }  // namespace
 
 template <typename T, int D>
 hipError_t launch_attn_bwd_fused(const BwdArgs& a, hipStream_t stream) {
-    constexpr int lds = KvCfg<T, D, true>::BYTES;
+    constexpr int lds = FusedCfg<T, D>::BYTES;
     const hipError_t e = ensure_dynamic_lds<&attn_bwd_fused<T, D>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_bwd_fused<T, D>), dim3(padded8(a.Hkv * a.B)), dim3(256), lds, stream, a);
@@ -786,10 +520,6 @@ template hipError_t launch_attn_bwd_fused<bf16, 128>(const BwdArgs&, hipStream_t
 
 template <typename T, int D>
 hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream) {
-    if constexpr (sizeof(T) == 4) {
-        const hipError_t e = set_bwd_lds_f32<D>();
-        if (e != hipSuccess) return e;
-    }
     if (phases & 1u) {
         const int64_t nblk = (int64_t)((a.S + kStatRows - 1) / kStatRows) * a.B * a.Hq;
         hipLaunchKernelGGL((attn_bwd_stats<T, D>), dim3((unsigned)nblk), dim3(256), 0, stream, a);
@@ -799,9 +529,8 @@ hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream
             const hipError_t ek = launch_attn_bwd_kv_bf16<D>(a, a.kv_tile, stream);
             if (ek != hipSuccess) return ek;
         } else {
-            const int n = (a.Skv + kKvBN - 1) / kKvBN * a.Hkv * a.B;
-            constexpr int lds = KvCfg<T, D, false>::BYTES;
-            hipLaunchKernelGGL((attn_bwd_kv<T, D>), dim3(padded8(n)), dim3(256), lds, stream, a);
+            const hipError_t ek = launch_attn_bwd_kv_f32<D>(a, stream);
+            if (ek != hipSuccess) return ek;
         }
     }
     if (phases & 4u) {
@@ -810,9 +539,8 @@ hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream
                 a.ds ? launch_attn_bwd_dq_bf16<D>(a, a.dq_tile, stream) : launch_attn_bwd_q_bf16<D>(a, stream);
             if (eq != hipSuccess) return eq;
         } else {
-            const int n = (a.S + kQBM - 1) / kQBM * a.Hq * a.B;
-            constexpr int lds = QSmem<T, D>::BYTES;
-            hipLaunchKernelGGL((attn_bwd_q<T, D>), dim3(padded8(n)), dim3(256), lds, stream, a);
+            const hipError_t eq = launch_attn_bwd_q_f32<D>(a, stream);
+            if (eq != hipSuccess) return eq;
         }
     }
     return hipGetLastError();

@@ -49,6 +49,12 @@ hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream
 template <typename T, int D>
 hipError_t launch_attn_bwd_fused(const BwdArgs& a, hipStream_t stream);
 
+// Backward passes for fp32 storage: dK and dV, and dQ (recomputing S and dP).
+template <int D>
+hipError_t launch_attn_bwd_kv_f32(const BwdArgs& a, hipStream_t stream);
+template <int D>
+hipError_t launch_attn_bwd_q_f32(const BwdArgs& a, hipStream_t stream);
+
 // Key/value-major backward pass for bf16 storage (software-pipelined kernel)
 // with kv tile `tile` of kAttnTiles (its split is a.kv_split).
 template <int D>

@@ -541,3 +541,24 @@ def test_binding_rejects_bad_lse_and_workspace():
     with pytest.raises(fbl.FblError):
         fbl.attn_bwd(q, q, q, o, q, lse, H, H, 0.125, False, workspace=ws[::2])
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("Sq,Skv,Hq,Hkv,mask", [(129, 129, 2, 1, 1), (160, 160, 4, 2, 3), (1, 300, 1, 1, 0),
+                                                (290, 131, 9, 3, 2), (257, 257, 8, 8, 1), (33, 417, 2, 2, 2)])
+def test_fp32_streams(Sq, Skv, Hq, Hkv, mask, d):
+    """The fp32 passes deal 32-row tiles to four wavefronts: walks of fewer tiles
+    than wavefronts, of one more than a multiple of four, ragged last tiles,
+    streams whose tiles are all masked, groups of heads.  Every key masked in
+    batch 0 of the padded ones."""
+    w = synth.Workload("fp32_streams", B=2, S=Sq, S_kv=Skv, Hq=Hq, Hkv=Hkv, d=d, dtype="f32", mask=mask, seed=Sq + d,
+                       len_lo=1, len_hi=Skv)
+    inp = synth.make_inputs(w)
+    if mask & synth.MASK_KEY_PADDING:
+        inp["kv_len"][0] = 0
+    note(f"fp32 streams Sq={Sq} Skv={Skv} Hq={Hq} Hkv={Hkv} d={d} mask={mask}")
+    got = gpu_fwd_bwd(inp)
+    errs, bad = compare(got, oracle_fwd_bwd(inp), "f32")
+    assert not bad, (bad, errs)
+    again = gpu_fwd_bwd(inp)
+    assert all(np.array_equal(got[n], again[n]) for n in got)
