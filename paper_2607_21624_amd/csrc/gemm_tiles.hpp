@@ -13,18 +13,23 @@ struct GemmTile {
 };
 
 // Index = the tile id of the C ABI.  Ids 0-3 are the named FBL_GEMM_TILE_*
-// shapes.
+// shapes.  Two wavefronts per SIMD and more cover each other's barriers, loads
+// and LDS reads: tile 9 with 8 wavefronts and 4 stages instead of 4 and 3 takes
+// 28.6 instead of 31.2 us (dX 512 x 2048 from 8192) and 9.9 instead of 11.7 (Y
+// 512 x 2048 from 2048); tile 4 with two workgroups of 8 wavefronts per CU
+// instead of one of 4 with 3 stages 24.0 instead of 30.7 us (Y 2000 x 4096 from
+// 1024) and 38.2 instead of 49.7 (dX 4096 x 2048 from 2048).
 constexpr GemmTile kGemmTiles[] = {
     {128, 128, 32, 3, 2, 2, 1},  // 0
     {128, 64, 32, 3, 2, 2, 1},   // 1
     {64, 128, 32, 3, 2, 2, 1},   // 2
     {64, 64, 32, 3, 2, 2, 1},    // 3
-    {128, 128, 64, 3, 2, 2, 1},  // 4
+    {128, 128, 64, 2, 2, 4, 1},  // 4: 8 wavefronts of 64 x 32, two workgroups per CU
     {128, 64, 64, 3, 2, 2, 1},   // 5
     {64, 128, 64, 3, 2, 2, 1},   // 6
     {64, 64, 64, 3, 2, 2, 1},    // 7
     {128, 128, 64, 4, 2, 2, 2},  // 8: 8 wavefronts, each 64 x 64 on half of every step
-    {64, 64, 128, 3, 1, 1, 4},   // 9: 4 wavefronts, each the whole 64 x 64 on a quarter
+    {64, 64, 128, 4, 2, 2, 2},   // 9: 8 wavefronts, each 32 x 32 on half
     {128, 64, 128, 3, 2, 1, 4},  // 10: 8 wavefronts, each 64 x 64 on a quarter
     {256, 128, 64, 3, 2, 2, 2},  // 11: 8 wavefronts, each 128 x 64 on half
     {128, 256, 64, 3, 2, 2, 2},  // 12: 8 wavefronts, each 64 x 128 on half
@@ -82,7 +87,7 @@ constexpr bool gemm_c2(const GemmTile& t, bool a_kmajor, bool b_nmajor, long lon
     return gemm_lds_bytes(t) <= kGemmLdsBytes && (a_row % kCacheLineBytes == 0 || a_row >= 2 * a_width) &&
            (b_row % kCacheLineBytes == 0 || b_row >= 2 * b_width);
 }
-constexpr long long gemm_padded(long long n, int tile) { return (n + tile - 1) / tile * tile; }
+constexpr long long gemm_padded(long long n, int tile) { return (n + tile - 1) & -(long long)tile; }  // powers of two
 constexpr bool gemm_c3(const GemmTile& t, long long rows, long long cols, long long kc) {
     return 10 * (gemm_padded(rows, t.bm) - rows) <= rows && 10 * (gemm_padded(cols, t.bn) - cols) <= cols &&
            10 * (gemm_padded(kc, t.bk) - kc) <= kc;

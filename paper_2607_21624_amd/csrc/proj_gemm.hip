@@ -92,7 +92,8 @@ struct GemmCfg {
                   "LDS read immediates fit 16 bits");
     static_assert(BYTES <= 160 * 1024 && NS * STAGE <= BYTES && (WK - 1) * WM * WN * PART <= BYTES, "LDS");
     static_assert((NS - 1) * LOADS < 64, "vmcnt range");
-    static constexpr int OCC = (NW == 4 && BYTES <= 80 * 1024) ? 2 : 1;
+    // wavefronts per SIMD the registers must allow: two workgroups per CU where LDS does
+    static constexpr int OCC = BYTES <= 80 * 1024 ? NW / 2 : NW / 4;
 };
 
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK, bool AT, bool BT>
@@ -240,24 +241,36 @@ proj_gemm_bf16(GemmArgs p) {
     for (int s = 0; s < nk; ++s) {
         wait_step(s);
         __syncthreads();
-        if (s + NS - 1 < nk) issue(s + NS - 1, buf == 0 ? NS - 1 : buf - 1);
         const uint32_t stage = (uint32_t)buf * C::STAGE;
         if (s == nfull) {  // the partial last step (every load of it has landed: nothing is in flight)
             zero_tail(stage, p.K - s * BK);
             __syncthreads();
         }
+        // The first chunk's LDS reads go out before the next loads: their
+        // latency passes under the issue of those (an issue of 4 .. 8 loads takes
+        // a wavefront 200 .. 400 cycles, a 32 x 32 x 128 step about 500 in all).
+        // 3 .. 8% on the small tiles: X A 512 x 16 from 2048 6.2 -> 5.9 us, 1000 x
+        // 2304 from 768 9.9 -> 9.4; nothing on the large ones.  More stages in LDS
+        // (8 instead of 3) where a CU has one workgroup made it slower (6.2 -> 7.2
+        // us): the loads' issue bounds a step, not their latency.
+        Frag<bf16> fa[2][TM], fb[2][TN];
+        auto read = [&](auto j_c) __attribute__((always_inline)) {
+            constexpr int J = decltype(j_c)::value;
 #pragma unroll
-        for (int j = 0; j < KCW; ++j) {
-            Frag<bf16> fa[TM], fb[TN];
+            for (int tm = 0; tm < TM; ++tm) fa[J & 1][tm] = frag_a(stage, tm, J);
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm) fa[tm] = frag_a(stage, tm, j);
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) fb[tn] = frag_b(stage, tn, j);
+            for (int tn = 0; tn < TN; ++tn) fb[J & 1][tn] = frag_b(stage, tn, J);
+        };
+        read(std::integral_constant<int, 0>{});
+        if (s + NS - 1 < nk) issue(s + NS - 1, buf == 0 ? NS - 1 : buf - 1);
+        unroll_steps(std::make_integer_sequence<int, KCW>{}, [&](auto j_c) __attribute__((always_inline)) {
+            constexpr int J = decltype(j_c)::value;
+            if constexpr (J + 1 < KCW) read(std::integral_constant<int, J + 1>{});
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) mma(acc[tn][tm], fb[tn], fa[tm]);
-        }
+                for (int tm = 0; tm < TM; ++tm) mma(acc[tn][tm], fb[J & 1][tn], fa[J & 1][tm]);
+        });
         buf = buf + 1 == NS ? 0 : buf + 1;
     }
 
