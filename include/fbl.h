@@ -462,12 +462,8 @@ fbl_status fbl_attn_bwd_noalloc(const fbl_layout* lq, const void* q, const fbl_l
  *            id in [0, fbl_gemm_tile_count()) (see fbl_gemm_tile_info;
  *            ids 0-3 have the names below, rows x cols of the op's output).
  *            AUTO takes the tile fbl_proj_tune measured best for this
- *            (op, M, K, N) in this process, else the first candidate (see
- *            fbl_proj_candidates) that gives at least 256 workgroups in a
- *            preference order set by the number of 128 x 128 output tiles
- *            (>= 1024: 4-wavefront tiles with small LDS; >= 256: the
- *            8-wavefront 128 x 128 tile; fewer: 64 x 64 tiles whose
- *            wavefronts split the contraction).
+ *            (op, M, K, N) in this process, else the untuned choice of
+ *            fbl_proj_auto_tile.
  * Supported: any number of output rows, output columns a multiple of 4 and
  * a contraction length a multiple of 8 (else FBL_ERR_UNSUPPORTED) -- so
  * ragged token counts and LoRA ranks (8, 16, ...) as the narrow side or the
@@ -566,10 +562,13 @@ void fbl_proj_tune_reset(void);
 /*
  * The tile id FBL_GEMM_TILE_AUTO resolves to (section 4.2's selection) for a
  * bf16 product (op, M, K,
- * N): the tuned choice when the table holds one, else the untuned preference
- * among the candidates -- by the number of 128 x 128 output tiles and the
- * contraction length, measured on MI355X.  The untuned choice depends on the
- * shape only (not on leading dimensions or pointers).  Pure host function.
+ * N): the tuned choice when the table holds one, else the untuned choice,
+ * measured on MI355X: from 384 output tiles of 128 x 128 a preference order
+ * among the candidates, by the number of those tiles and the contraction
+ * length, where the modelled time of another tile is not well below it; for
+ * smaller outputs the tile of least modelled time, a candidate unless another
+ * tile is clearly faster.  The untuned choice depends on the shape only (not
+ * on leading dimensions or pointers).  Pure host function.
  * FBL_ERR_NULL, FBL_ERR_ARG (unknown op) or FBL_ERR_SHAPE on bad arguments.
  */
 fbl_status fbl_proj_auto_tile(uint32_t op, int64_t M, int64_t K, int64_t N, int32_t* tile);

@@ -19,6 +19,7 @@
 
 #include "../../include/fbl.h"
 #include "attn_tiles.hpp"
+#include "gemm_cost.hpp"
 #include "kernels.hpp"
 
 using fbl::bf16;
@@ -970,26 +971,30 @@ int32_t tuned_tile(uint32_t op, int64_t M, int64_t K, int64_t N) {
     return it == g_tuned.end() ? -1 : it->second;
 }
 
-// Untuned choice among the candidates, by how many 128 x 128 output tiles
-// the product has (n128) and how long its contraction is -- measured on the
-// 512 x {2048, 4096} x {8192, 12288}, {1024, 2048} x 4096 x 4096 and 4096 x
-// 4096 x {4096, 12288} products and their transposes:
+// Untuned choice.  Below 384 output tiles of 128 x 128 (n128) the tile of
+// least modelled time (gemm_cost.hpp), from the ten that the model ever needs,
+// in an order of preference among equals (3%):
+//   a candidate is kept unless another tile is 5% and 0.6 us faster -- what the
+//     filters leave out (32-column tiles that stage 64-byte rows, padding past
+//     10%) is often still the faster one for a deep contraction: Y 256 x 1024
+//     from 4096 takes 22 us on the candidates' 128 x 64 tile, 9.6 on 32 x 32;
+//   outputs of fewer than 32 rows keep to the candidates.
+// From n128 = 384 the orders that were measured on the 512 x {2048, 4096} x
+// {8192, 12288}, {1024, 2048} x 4096 x 4096 and 4096 x 4096 x {4096, 12288}
+// products and their transposes stand, unless the model is 12% below them (Y
+// 4096 x 3072 from 2048: 72 us on 384 workgroups of 256 x 128, 57 on 192 of
+// 256 x 256):
 //   n128 >= 1024, contraction >= 2048: the 256 x 256 tiles, 8 wavefronts
 //     first when A is read along its rows, 4 first for the weight gradient's
 //     transposed A;
 //   n128 >= 1024, shorter contraction: 4-wavefront 128 x 128 tiles (for the
-//     weight gradient 3-4% ahead of the 256 x 256 tiles, timed interleaved);
+//     weight gradient 3-4% ahead of the 256 x 256 tiles, timed interleaved), the
+//     first that gives at least one workgroup per CU (256);
 //   384 <= n128 < 1024: the 8-wavefront 256 x 128 (forward) or 128 x 256
 //     (data gradient) tile, even below one workgroup per CU (two waves per
 //     SIMD do more for these than a full grid of 4-wavefront tiles); for the
 //     weight gradient's transposed A the 4-wavefront 128 x 128 tile, then
-//     128 x 256;
-//   256 <= n128 < 384: 4-wavefront 64 x 128 and 128 x 64 tiles;
-//   below: the 8-wavefront 128 x 64 tile that splits a deep contraction four
-//     ways, then the 4-wavefront 64 x 64 one.
-// Orders marked `fill` take the first candidate that gives at least one
-// workgroup per CU (256), else the first candidate; the others take the
-// first candidate.
+//     128 x 256.
 int32_t default_tile(const ProjPlan& pl) {
     static const int big[] = {19, 18, 20, 17, 11, 12, 8, 4, 0, 6, 5, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16};
     static const int big_t[] = {18, 20, 19, 17, 11, 12, 8, 4, 0, 6, 5, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16};
@@ -997,34 +1002,51 @@ int32_t default_tile(const ProjPlan& pl) {
     static const int wide[] = {11, 12, 8, 4, 0, 5, 6, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16, 17, 18, 19, 20};
     static const int wide_d[] = {12, 11, 8, 4, 0, 5, 6, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16, 17, 18, 19, 20};
     static const int wide_t[] = {0, 12, 8, 11, 4, 5, 6, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16, 17, 18, 19, 20};
-    static const int some[] = {6, 5, 8, 4, 11, 12, 0, 2, 1, 10, 9, 7, 3, 13, 15, 14, 16, 17, 18, 19, 20};
-    static const int few[] = {10, 9, 7, 6, 5, 8, 4, 3, 2, 1, 0, 11, 12, 14, 13, 15, 16, 17, 18, 19, 20};
-    static_assert(sizeof(many) == sizeof(int) * fbl::kGemmTileCount && sizeof(some) == sizeof(many) &&
-                      sizeof(few) == sizeof(many) && sizeof(big) == sizeof(many) && sizeof(big_t) == sizeof(many) &&
-                      sizeof(wide) == sizeof(many) && sizeof(wide_d) == sizeof(many) && sizeof(wide_t) == sizeof(many),
+    static_assert(sizeof(many) == sizeof(int) * fbl::kGemmTileCount && sizeof(big) == sizeof(many) &&
+                      sizeof(big_t) == sizeof(many) && sizeof(wide) == sizeof(many) && sizeof(wide_d) == sizeof(many) &&
+                      sizeof(wide_t) == sizeof(many),
                   "every tile ranked once");
+    static const int modelled[] = {19, 6, 7, 9, 10, 4, 14, 16, 15, 8};
     const uint64_t cand = candidate_set(pl);
+    const int product = pl.a_kmajor ? 2 : pl.b_nmajor ? 1 : 0;
+    double costs[fbl::kGemmTileCount] = {};  // 0: not evaluated yet
+    const auto cost = [&](int t) {
+        if (costs[t] == 0) costs[t] = fbl::gemm_cost(t, product, pl.orows, pl.ocols, pl.kc);
+        return costs[t];
+    };
+    // the first of the modelled tiles in `among` within 3% of the least time
+    const auto fastest = [&](uint64_t among) {
+        double least = HUGE_VAL;
+        for (int t : modelled)
+            if (among >> t & 1) least = std::min(least, cost(t));
+        for (int t : modelled)
+            if ((among >> t & 1) && cost(t) <= 1.03 * least) return t;
+        return -1;
+    };
+    int32_t pick = fastest(~uint64_t(0));
+    int32_t kept = fastest(cand);
+    if (kept < 0)  // none of the modelled tiles is a candidate
+        for (int t = 0; t < fbl::kGemmTileCount; ++t)
+            if ((cand >> t & 1) && (kept < 0 || cost(t) < cost(kept))) kept = t;
+    if (kept >= 0 && (pl.orows < 32 || cost(kept) < std::max(1.05 * cost(pick), cost(pick) + 0.6))) pick = kept;
+
     const int64_t n128 = ((pl.orows + 127) / 128) * ((pl.ocols + 127) / 128);
-    const int* order;
-    bool fill = true;
-    if (n128 >= 1024) {
-        order = pl.kc >= 2048 ? (pl.a_kmajor ? big_t : big) : many;
-    } else if (n128 >= 384) {
-        order = pl.a_kmajor ? wide_t : (pl.b_nmajor ? wide_d : wide);
-        fill = false;
-    } else {
-        order = n128 >= 256 ? some : few;
-    }
+    if (n128 < 384) return pick;
+    const bool fill = n128 >= 1024;  // take the first that gives every CU a workgroup, else the first
+    const int* order = !fill ? (pl.a_kmajor ? wide_t : (pl.b_nmajor ? wide_d : wide))
+                             : (pl.kc >= 2048 ? (pl.a_kmajor ? big_t : big) : many);
     int32_t first = -1;
     for (int i = 0; i < fbl::kGemmTileCount; ++i) {
         const int t = order[i];
         if (!(cand >> t & 1)) continue;
-        if (!fill) return t;
-        const fbl::GemmTile& g = fbl::kGemmTiles[t];
-        if (((pl.orows + g.bm - 1) / g.bm) * ((pl.ocols + g.bn - 1) / g.bn) >= 256) return t;
         if (first < 0) first = t;
+        const fbl::GemmTile& g = fbl::kGemmTiles[t];
+        if (!fill || ((pl.orows + g.bm - 1) / g.bm) * ((pl.ocols + g.bn - 1) / g.bn) >= 256) {
+            first = t;
+            break;
+        }
     }
-    return first >= 0 ? first : order[0];
+    return first >= 0 && cost(first) <= 1.12 * cost(pick) ? first : pick;
 }
 
 }  // namespace

@@ -306,3 +306,24 @@ def test_auto_tile_query_matches_dispatch(op, M, K, N):
     named = fbl.proj(op, a, b, tile=t)
     torch.cuda.synchronize()
     assert torch.equal(auto, named)
+
+
+@pytest.mark.parametrize("op,M,K,N", [(0, 256, 4096, 1024), (0, 136, 1088, 1152), (2, 1896, 704, 64), (1, 104, 520, 968),
+                                      (0, 1000, 768, 2304), (2, 1000, 768, 2304), (0, 40, 72, 40), (2, 8, 24, 4104)])
+def test_auto_tile_products(op, M, K, N):
+    """FBL_GEMM_TILE_AUTO where the modelled choice decides -- outside the
+    candidates too (32-column tiles with a deep contraction) -- on ragged
+    extents: the oracle's product, and the named tile's bits."""
+    import torch
+    fbl = _lib()
+    fbl.proj_tune_reset()
+    x, w, dy = _inputs(M, K, N, 7 + op)
+    a, b, ref = {0: (x, w, oracle.proj_fwd), 1: (dy, w, oracle.proj_bwd_data), 2: (x, dy, oracle.proj_bwd_weight)}[op]
+    A, B = to_dev(a, "bf16"), to_dev(b, "bf16")
+    t = fbl.proj_auto_tile(op, M, K, N)
+    note(f"auto product op={op} M={M} K={K} N={N} -> t{t}")
+    got = fbl.proj(op, A, B)
+    named = fbl.proj(op, A, B, tile=t)
+    torch.cuda.synchronize()
+    assert torch.equal(got, named)
+    assert rel_err(to_np(got), ref(a, b)) <= TOL
