@@ -1,10 +1,14 @@
-"""Build libfbl.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Build libfbl.so (HIP kernels + C ABI) for gfx950 with hipcc, and _fastcall.so
+(the binding's native call path, host code against torch's headers) with g++,
+in-tree.
 
 Each source compiles to its own object in parallel (paper_2607_21624_amd/_build/),
-then one link step writes libfbl.so."""
+then one link step writes libfbl.so and one _fastcall.so."""
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -22,6 +26,26 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
+FASTCALL = os.path.join(HERE, "_fastcall.so")
+CXX = os.environ.get("CXX", "g++")
+
+
+def _torch_dir() -> str:
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def _fastcall_compile(obj: str):
+    t = _torch_dir()
+    return [CXX, "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+            "-c", "-o", obj, os.path.join(CSRC, "fastcall.cpp")]
+
+
+def _fastcall_link(obj: str, out: str):
+    return [CXX, "-shared", "-o", out, obj, "-L", HERE, "-l:libfbl.so", "-L", os.path.join(_torch_dir(), "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
+
 
 def _run(cmd, verbose):
     if verbose:
@@ -29,19 +53,24 @@ def _run(cmd, verbose):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed: " + " ".join(cmd[-3:]))
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed: " + " ".join(cmd[-3:]))
 
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     objs = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]
     jobs = [[HIPCC, *FLAGS, "-c", "-o", o, os.path.join(CSRC, s)] for s, o in zip(SOURCES, objs)]
+    fast_obj = os.path.join(OBJ, "fastcall.o")
+    jobs.append(_fastcall_compile(fast_obj))
     workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
     with ThreadPoolExecutor(workers) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)
+    tmp = FASTCALL + ".tmp"
+    _run(_fastcall_link(fast_obj, tmp), verbose)
+    os.replace(tmp, FASTCALL)
     return LIB
 
 

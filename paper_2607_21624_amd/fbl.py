@@ -1,7 +1,7 @@
 """ctypes binding of libfbl.so (the C ABI in include/fbl.h).
 
-Argument marshalling only: every step of the attention path runs in the HIP
-kernels behind the C ABI.  torch is used for device memory (allocating outputs
+Argument marshalling only, natively for the plain tensor calls (_fastcall.so):
+every step of the attention path runs in the HIP kernels behind the C ABI.  torch is used for device memory (allocating outputs
 and the workspace) and for the current stream.  If libfbl.so is missing the
 import fails; there is no fallback implementation.
 """
@@ -175,6 +175,12 @@ def _load() -> ctypes.CDLL:
 
 
 LIB = _load()
+
+# The plain calls of attn_fwd, attn_bwd, their packed forms and proj run natively
+# (csrc/fastcall.cpp): each does the whole call, or nothing and returns None --
+# any argument that is not a plain one, any error -- and the Python below then
+# makes the call with every check.
+from . import _fastcall as _FAST  # noqa: E402  (needs libfbl.so's runtime loaded first)
 
 
 def status_str(status: int) -> str:
@@ -394,6 +400,9 @@ def attn_fwd(q, k, v, Hq: int, Hkv: int, scale: Optional[float] = None, causal: 
              out=None, lse=None, stream=None, tile: int = FBL_ATTN_TILE_AUTO):
     """Forward on token-major tensors.  Returns (O, LSE); O has q's shape and dtype
     (allocated contiguous unless `out` is given), LSE is float32 [B, Hq, S]."""
+    done = _FAST.attn_fwd(q, k, v, Hq, Hkv, scale, causal, kv_len, out, lse, stream, tile)
+    if done is not None:
+        return done
     import torch
     _check_kv_len(kv_len, q.shape[0], "attn_fwd")
     _check_device("attn_fwd", stream, q=q, k=k, v=v, kv_len=kv_len, out=out, lse=lse)
@@ -417,6 +426,10 @@ def attn_bwd(q, k, v, o, do, lse, Hq: int, Hkv: int, scale: Optional[float] = No
              kv_len=None, dq=None, dk=None, dv=None, workspace=None, stream=None, phases: int = FBL_BWD_ALL,
              kv_tile: int = FBL_ATTN_TILE_AUTO, dq_tile: int = FBL_ATTN_TILE_AUTO):
     """Backward.  Returns (dQ, dK, dV) with the shapes/dtypes of q, k, v."""
+    done = _FAST.attn_bwd(q, k, v, o, do, lse, Hq, Hkv, scale, causal, kv_len, dq, dk, dv, workspace, stream, phases,
+                          kv_tile, dq_tile)
+    if done is not None:
+        return done
     import torch
     _check_kv_len(kv_len, q.shape[0], "attn_bwd")
     _check_device("attn_bwd", stream, q=q, k=k, v=v, o=o, do=do, lse=lse, kv_len=kv_len, dq=dq, dk=dk, dv=dv,
@@ -583,6 +596,9 @@ def attn_fwd_packed(qkv, Hq: int, Hkv: int, scale: Optional[float] = None, causa
     """Forward on a packed QKV projection output [B, S, (Hq + 2 Hkv) D]: Q, K and
     V are read in place through fbl_layout_packed_qkv descriptors.  Returns
     (O [B, S, Hq D], LSE [B, Hq, S])."""
+    done = _FAST.attn_fwd_packed(qkv, Hq, Hkv, scale, causal, kv_len, out, lse, stream)
+    if done is not None:
+        return done
     import torch
     _check_kv_len(kv_len, qkv.shape[0], "attn_fwd_packed")
     _check_device("attn_fwd_packed", stream, qkv=qkv, kv_len=kv_len, out=out, lse=lse)
@@ -606,6 +622,9 @@ def attn_bwd_packed(qkv, o, do, lse, Hq: int, Hkv: int, scale: Optional[float] =
                     kv_len=None, dqkv=None, workspace=None, stream=None):
     """Backward on a packed QKV projection output: dQ, dK, dV are written into
     one packed gradient tensor shaped like ``qkv`` (allocated unless given)."""
+    done = _FAST.attn_bwd_packed(qkv, o, do, lse, Hq, Hkv, scale, causal, kv_len, dqkv, workspace, stream)
+    if done is not None:
+        return done
     import torch
     _check_kv_len(kv_len, qkv.shape[0], "attn_bwd_packed")
     _check_device("attn_bwd_packed", stream, qkv=qkv, o=o, do=do, lse=lse, kv_len=kv_len, dqkv=dqkv,
@@ -660,6 +679,9 @@ def proj(op: int, a, b, out=None, tile: int = FBL_GEMM_TILE_AUTO, stream=None):
     FBL_PROJ_FWD (a = X [M, K], b = W [K, N]) -> Y [M, N];
     FBL_PROJ_BWD_DATA (a = dY [M, N], b = W [K, N]) -> dX [M, K];
     FBL_PROJ_BWD_WEIGHT (a = X [M, K], b = dY [M, N]) -> dW [K, N]."""
+    done = _FAST.proj(op, a, b, out, tile, stream)
+    if done is not None:
+        return done
     import torch
     _check_device("proj", stream, a=a, b=b, out=out)
     M, K, N, shape, lda, ldb = _proj_shape(op, a, b)
