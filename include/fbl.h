@@ -171,7 +171,9 @@ fbl_status fbl_layout_map_device(const fbl_layout* l, int64_t* out, void* stream
  * grouped-query head map described above, and the row log-sum-exp saved for
  * the backward.  QK^T and the product with V are the consecutive
  * matrix-product pair of section 4.4.2, fused in one kernel.  bf16 storage
- * runs the forward tile FBL_ATTN_TILE_AUTO resolves to (fbl_attn_auto_tiles).
+ * runs the forward tile FBL_ATTN_TILE_AUTO resolves to (fbl_attn_auto_tiles),
+ * or, for small calls of a shape fbl_attn_tune has not measured, a kernel of 32
+ * queries per workgroup (same results up to rounding order).
  *   lq/q     queries, Hq heads.       lk/k, lv/v  keys and values, Hkv heads.
  *   lo/o     output, same extents as q.
  *   lse      float32 [B, Hq, S_q] contiguous, written (saved for the backward).
@@ -249,11 +251,15 @@ fbl_status fbl_attn_bwd_workspace_min(const fbl_layout* lq, const fbl_layout* lk
  * Up to 128 keys (S_kv <= 128; fp32 storage only at D <= 64), when there are
  * at least 128 (batch, key/value head) pairs or each pair has at most 64
  * query blocks (Hq/Hkv * ceil(S_q / 64), ceil(S_q / 32) at D = 128), the
- * backward is one launch: a workgroup holds all keys of one (batch, key/value head) in
- * LDS and, per block of queries of its group, forms D_i, the dK and dV
- * contributions and the block's dS, and contracts that dS with K into dQ --
- * no workspace is read or written.  Its results agree with the three-launch
- * path of fbl_attn_bwd_phases up to rounding order, not bit for bit.
+ * backward is one launch; from 136 keys on it is one where that is the faster
+ * (fp32 storage at D <= 64, small and mid-sized calls otherwise; not for shapes
+ * fbl_attn_tune has measured).  Either a workgroup holds all keys of one (batch,
+ * key/value head) in LDS and, per block of queries of its group, forms D_i, the
+ * dK and dV contributions and the block's dS, and contracts that dS with K into
+ * dQ, or workgroups of 32 keys and of 32 queries form dK and dV, and dQ, each
+ * with the D_i it needs -- no workspace is read or written.  Its results agree
+ * with the three-launch path of fbl_attn_bwd_phases up to rounding order, not
+ * bit for bit.
  */
 fbl_status fbl_attn_bwd(const fbl_layout* lq, const void* q, const fbl_layout* lk, const void* k,
                         const fbl_layout* lv, const void* v, const fbl_layout* lo, const void* o,

@@ -127,7 +127,16 @@ fbl_status check_qkv(const fbl_layout* lq, const void* q, const fbl_layout* lk, 
     return FBL_OK;
 }
 
+constexpr int32_t kFwdStreams = -2;  // no tile: the kernel of 32 queries per workgroup
+
 hipError_t dispatch_fwd(int32_t dtype, int D, int tile, const fbl::FwdArgs& a, hipStream_t s) {
+    if (dtype == FBL_BF16 && tile == kFwdStreams) {
+        switch (D) {
+            case 32: return fbl::launch_attn_fwd_streams<bf16, 32>(a, s);
+            case 64: return fbl::launch_attn_fwd_streams<bf16, 64>(a, s);
+            default: return fbl::launch_attn_fwd_streams<bf16, 128>(a, s);
+        }
+    }
     if (dtype == FBL_BF16) {
         switch (D) {
             case 32: return fbl::launch_attn_fwd_bf16<32>(a, tile, s);
@@ -136,9 +145,9 @@ hipError_t dispatch_fwd(int32_t dtype, int D, int tile, const fbl::FwdArgs& a, h
         }
     }
     switch (D) {
-        case 32: return fbl::launch_attn_fwd_f32<32>(a, s);
-        case 64: return fbl::launch_attn_fwd_f32<64>(a, s);
-        default: return fbl::launch_attn_fwd_f32<128>(a, s);
+        case 32: return fbl::launch_attn_fwd_streams<float, 32>(a, s);
+        case 64: return fbl::launch_attn_fwd_streams<float, 64>(a, s);
+        default: return fbl::launch_attn_fwd_streams<float, 128>(a, s);
     }
 }
 
@@ -150,6 +159,38 @@ hipError_t dispatch_bwd_fused(int32_t dtype, int D, const fbl::BwdArgs& a, hipSt
         case 64: return fbl::launch_attn_bwd_fused<bf16, 64>(a, s);
         default: return fbl::launch_attn_bwd_fused<bf16, 128>(a, s);
     }
+}
+
+hipError_t dispatch_bwd_streams(int32_t dtype, int D, const fbl::BwdArgs& a, hipStream_t s) {
+    if (dtype == FBL_F32) {
+        switch (D) {
+            case 32: return fbl::launch_attn_bwd_streams<float, 32>(a, s);
+            case 64: return fbl::launch_attn_bwd_streams<float, 64>(a, s);
+            default: return fbl::launch_attn_bwd_streams<float, 128>(a, s);
+        }
+    }
+    switch (D) {
+        case 32: return fbl::launch_attn_bwd_streams<bf16, 32>(a, s);
+        case 64: return fbl::launch_attn_bwd_streams<bf16, 64>(a, s);
+        default: return fbl::launch_attn_bwd_streams<bf16, 128>(a, s);
+    }
+}
+
+int64_t blocks32(int64_t n) { return (n + 31) / 32; }
+
+// Forward, bf16: 32 queries per workgroup with the keys dealt to its four
+// wavefronts, instead of a tile of 128 queries.  It wins while its workgroups
+// (half of their work under a causal mask) are at most about two per CU, so
+// that the length of a wavefront's walk decides; beyond that the tiles, which
+// stage each key block for four times the queries.  With one or two key blocks
+// of 32 most of its wavefronts have none.  Measured (us, tile -> 32 queries; d
+// = 64): B8 H12 S128 7.4 -> 6.2, B1 H16 S1024 causal 16.6 -> 9.8, B2 H16 S1024
+// causal (512) 16.9 -> 15.7, B4 H12 S1024 causal (768) 19.1 -> 18.8, B5 H32 S304
+// causal (800) 11.8 -> 15.0.  d = 128, whose state allows two wavefronts per SIMD:
+// B2 H20 S412 causal (260) 14.2 -> 12.8, B3 H16 S439 causal (336) 14.4 -> 15.4.
+bool fwd_streams(const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind) {
+    const int64_t work = lq->B * lq->H * blocks32(lq->S) / ((mask_kind & FBL_MASK_CAUSAL) ? 2 : 1);
+    return blocks32(lk->S) >= 3 && work <= (lq->D == 128 ? 300 : 512);
 }
 
 // Key/value sequences up to this length fit one kv workgroup (four
@@ -167,6 +208,49 @@ bool bwd_fuses(const fbl_layout* lq, const fbl_layout* lk) {
     const int64_t bq = lq->D == 128 ? 32 : 64;  // query rows per block of the fused pass
     const int64_t blocks = lq->H / lk->H * ((lq->S + bq - 1) / bq);
     return lq->B * lk->H >= 128 || blocks <= 64;
+}
+
+// Backward in one launch, 32 keys or 32 queries per workgroup.  Up to 128 keys it
+// stands beside the fused pass (bwd_fuses), which holds a pair's keys in one
+// workgroup: faster once the pairs alone fill the chip.  Measured (us, fused
+// -> 32 rows): bf16 d = 64 B8 H12 S128 (384 key blocks) 16.1 -> 9.3, B8 H32 S128
+// (1024) 14.6 -> 21.1; d = 128 H32 S128 (128) 22.7 -> 9.8, B8 (1024) 28 -> 61; fp32
+// d = 64 B4 H16 S128 (256) 38 -> 16, B16 (1024) 43 -> 53.
+bool streams_over_fused(const fbl_layout* lq, const fbl_layout* lk) {
+    return lq->B * lk->H * blocks32(lk->S) <= (lq->D == 128 ? 256 : 512);
+}
+
+// Beyond 128 keys, instead of statistics, key/value and dQ passes.  The three
+// launches share their tiles among four times the rows, and bf16 contracts a
+// stored dS; one launch of 32-row workgroups has no gaps and no long chains.
+// Both are modelled in us, fitted to 75 bf16 shapes of 129 .. 4096 keys (rms error 9
+// .. 16%); with the margin no shape measured got slower:
+//   one launch  start + max(step * query blocks of a kv group,
+//                           block * 32 x 32 blocks of scores + wg * workgroups)
+//   three       start + q * query blocks + block * blocks + group * min(group's, 40)
+// fp32 has no stored dS to lose: one launch at every size up to d = 64 (B2 H12
+// S500 causal 59 -> 45, B4 H16/4 S1024 causal 331 -> 269, B1 H16 S1024 129 -> 127);
+// at d = 128, one wavefront per SIMD, up to one workgroup per CU (H8 S256 50 ->
+// 27, B2 H8 S1024 172 -> 180).
+// (129 .. 135 keys keep three launches: their count there is documented.)
+bool bwd_streams(const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind) {
+    if (lk->S < 136) return false;
+    const int64_t nq = blocks32(lq->S), nk = blocks32(lk->S);
+    const double wgs = (double)(lq->B * lk->H * nk + lq->B * lq->H * nq);
+    if (lq->dtype != FBL_BF16) return lq->D <= 64 || wgs <= 256;
+    struct Cost { double start, step, block, wg, start3, q3, block3, group3; };
+    static const Cost costs[3] = {
+        {4.2, 0.271, 0.83e-3, 2.5e-3, 15.4, 0.439, 0.90e-3, 0.025},   // d = 32
+        {5.3, 0.402, 1.02e-3, 6.7e-3, 17.9, 0.445, 1.04e-3, 0.068},   // 64
+        {6.5, 0.691, 4.47e-3, 20.7e-3, 21.9, 0.303, 2.69e-3, 0.300},  // 128
+    };
+    const Cost& c = costs[lq->D == 32 ? 0 : lq->D == 64 ? 1 : 2];
+    double blocks = (double)(lq->B * lq->H) * (double)nq * (double)nk;
+    if (mask_kind & FBL_MASK_CAUSAL) blocks *= (double)(nq + 1) / (double)(2 * nq);
+    const double group = (double)(lq->H / lk->H) * (double)nq;
+    const double one = c.start + std::max(c.step * group, c.block * blocks + c.wg * wgs);
+    const double three = c.start3 + c.q3 * (double)nq + c.block3 * blocks + c.group3 * std::min(group, 40.0);
+    return one < 0.85 * three;
 }
 
 template <typename T>
@@ -269,7 +353,7 @@ int32_t attn_default_tile(uint32_t pass, const fbl_layout* lq, const fbl_layout*
 // The tile a launch runs: an explicit id (legal for the pass at this head
 // dim), else the measured choice for the shape, else the untuned default.
 fbl_status attn_resolve(uint32_t pass, const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind,
-                        int32_t requested, int32_t* out) {
+                        int32_t requested, int32_t* out, bool* measured = nullptr) {
     if (requested != FBL_ATTN_TILE_AUTO) {
         if (requested < 0 || requested >= fbl::kAttnTileCount || (uint32_t)fbl::kAttnTiles[requested].pass != pass)
             return FBL_ERR_ARG;
@@ -282,6 +366,7 @@ fbl_status attn_resolve(uint32_t pass, const fbl_layout* lq, const fbl_layout* l
         const auto it = g_attn_tuned.find(attn_key(pass, lq, lk, mask_kind));
         if (it != g_attn_tuned.end()) {
             *out = it->second;
+            if (measured) *measured = true;
             return FBL_OK;
         }
     }
@@ -460,7 +545,9 @@ fbl_status fbl_attn_fwd_tiled(const fbl_layout* lq, const void* q, const fbl_lay
     if (overlaps(o, span_bytes(lo), lse, lse_bytes)) return FBL_ERR_ARG;
     int32_t t = -1;
     if (lq->dtype == FBL_BF16) {
-        if ((st = attn_resolve(FBL_ATTN_FWD, lq, lk, mask.kind, tile, &t)) != FBL_OK) return st;
+        bool measured = false;
+        if ((st = attn_resolve(FBL_ATTN_FWD, lq, lk, mask.kind, tile, &t, &measured)) != FBL_OK) return st;
+        if (tile == FBL_ATTN_TILE_AUTO && !measured && fwd_streams(lq, lk, mask.kind)) t = kFwdStreams;
     } else if (tile != FBL_ATTN_TILE_AUTO) {
         return FBL_ERR_ARG;  // fp32 storage has one configuration
     }
@@ -517,7 +604,8 @@ namespace {
 // What a backward call runs, from the shapes, the mask, the workspace size
 // and the requested tiles alone (no pointer is read).
 struct BwdPlan {
-    bool fused = false;      // the one-launch backward
+    bool fused = false;      // one launch, a pair's keys per workgroup (up to 128)
+    bool streams = false;    // one launch, 32 keys or queries per workgroup
     bool stores_ds = false;  // the kv pass stores dS, the dQ pass reads it
     int kv_split = 1;        // key/value pass split (partial sums + reduction)
     int32_t kv_tile = 5, dq_tile = 7;
@@ -526,16 +614,20 @@ struct BwdPlan {
 fbl_status bwd_plan(uint32_t phases, const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind,
                     size_t ws_bytes, int32_t kv_tile, int32_t dq_tile, BwdPlan* p) {
     fbl_status st;
+    bool tuned[2] = {false, false};
     // tiles of the bf16 passes (fp32 storage has one configuration per pass)
     if (lq->dtype == FBL_BF16) {
-        if ((st = attn_resolve(FBL_ATTN_BWD_KV, lq, lk, mask_kind, kv_tile, &p->kv_tile)) != FBL_OK) return st;
-        if ((st = attn_resolve(FBL_ATTN_BWD_DQ, lq, lk, mask_kind, dq_tile, &p->dq_tile)) != FBL_OK) return st;
+        if ((st = attn_resolve(FBL_ATTN_BWD_KV, lq, lk, mask_kind, kv_tile, &p->kv_tile, &tuned[0])) != FBL_OK) return st;
+        if ((st = attn_resolve(FBL_ATTN_BWD_DQ, lq, lk, mask_kind, dq_tile, &p->dq_tile, &tuned[1])) != FBL_OK) return st;
     } else if (kv_tile != FBL_ATTN_TILE_AUTO || dq_tile != FBL_ATTN_TILE_AUTO) {
         return FBL_ERR_ARG;
     }
-    // the whole backward with automatic tiles, keys within one kv workgroup: one fused launch
-    p->fused = phases == FBL_BWD_ALL && bwd_fuses(lq, lk) && kv_tile == FBL_ATTN_TILE_AUTO &&
-               dq_tile == FBL_ATTN_TILE_AUTO;
+    // the whole backward with automatic tiles: one launch up to 128 keys and, where
+    // no tile has been measured for the shape, beyond them
+    if (phases == FBL_BWD_ALL && kv_tile == FBL_ATTN_TILE_AUTO && dq_tile == FBL_ATTN_TILE_AUTO) {
+        if (bwd_fuses(lq, lk)) p->streams = streams_over_fused(lq, lk), p->fused = !p->streams;
+        else p->streams = !tuned[0] && !tuned[1] && bwd_streams(lq, lk, mask_kind);
+    }
     // stored-dS path when the workspace holds the dS blocks, else recompute
     const size_t ds_bytes = ws_ds_bytes(lq, lk);
     p->stores_ds = ds_bytes && ws_bytes >= ws_stats_bytes(lq) + ds_bytes;
@@ -628,7 +720,9 @@ fbl_status bwd_run(uint32_t phases, const fbl_layout* lq, const void* q, const f
     a.mask = mask_args(mask);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (plan.fused)
+    if (plan.streams)
+        e = dispatch_bwd_streams(lq->dtype, (int)lq->D, a, s);
+    else if (plan.fused)
         e = dispatch_bwd_fused(lq->dtype, (int)lq->D, a, s);
     else
         e = lq->dtype == FBL_BF16 ? dispatch_bwd<bf16>((int)lq->D, a, phases, s)
@@ -670,7 +764,7 @@ fbl_status fbl_attn_bwd_launches(uint32_t phases, const fbl_layout* lq, const fb
     if (lq->D != 32 && lq->D != 64 && lq->D != 128) return FBL_ERR_UNSUPPORTED;
     BwdPlan plan;
     if ((st = bwd_plan(phases, lq, lk, mask_kind, ws_bytes, kv_tile, dq_tile, &plan)) != FBL_OK) return st;
-    if (plan.fused) {
+    if (plan.fused || plan.streams) {
         *launches = 1;
         return FBL_OK;
     }

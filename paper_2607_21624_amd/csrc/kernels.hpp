@@ -30,9 +30,9 @@ hipError_t ensure_dynamic_lds(int bytes) {
 
 typedef __bf16 bf16;
 
-// Forward for fp32 storage: O and LSE from Q, K, V; D in {32, 64, 128}.
-template <int D>
-hipError_t launch_attn_fwd_f32(const FwdArgs& a, hipStream_t stream);
+// Forward, 32 queries per workgroup: O and LSE from Q, K, V; D in {32, 64, 128}.
+template <typename T, int D>
+hipError_t launch_attn_fwd_streams(const FwdArgs& a, hipStream_t stream);
 
 // Forward for bf16 storage with forward tile `tile` of kAttnTiles.
 template <int D>
@@ -44,8 +44,13 @@ hipError_t launch_attn_fwd_bf16(const FwdArgs& a, int tile, hipStream_t stream);
 template <typename T, int D>
 hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream);
 
-// The whole backward in one launch, for key/value sequences of at most 128
-// tokens (one key block per (batch, kv head)): row statistics, dK, dV and dQ.
+// The whole backward in one launch, 32 keys or 32 queries per workgroup: dK and
+// dV, and dQ (recomputing S and dP), each with its row statistics.
+template <typename T, int D>
+hipError_t launch_attn_bwd_streams(const BwdArgs& a, hipStream_t stream);
+
+// The same for key/value sequences of at most 128 tokens, one workgroup per
+// (batch, kv head); fp32 at D = 32 and 64 only.
 template <typename T, int D>
 hipError_t launch_attn_bwd_fused(const BwdArgs& a, hipStream_t stream);
 
