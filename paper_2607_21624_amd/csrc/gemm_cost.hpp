@@ -14,6 +14,9 @@
 // (default_tile in api.cpp) is 2.7% slower than the best of the 21 in the
 // geometric mean and within 7% on 9 of 10 products; the preference orders alone
 // were 24% slower, within 70% on 9 of 10.
+// (The loads have since been spread over a step's products, proj_gemm.hip: on 130
+// other shapes the pick is 5.9% from the best, 4.7 .. 5.4% with constants fitted
+// again -- inside what two timings of such a sweep differ by, so they stay.)
 #pragma once
 
 #include "gemm_tiles.hpp"

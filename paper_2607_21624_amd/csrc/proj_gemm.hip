@@ -124,12 +124,17 @@ proj_gemm_bf16(GemmArgs p) {
     typename TB::Dma db;
     da.init((uint32_t)(p.lda * 2), wave, lane);
     db.init((uint32_t)(p.ldb * 2), wave, lane);
-    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+    auto a_off = [&](int s) __attribute__((always_inline)) {
         const int k0 = s * BK;
-        const uint32_t sa = (uint32_t)((AT ? (int64_t)k0 * p.lda + m0 : (int64_t)m0 * p.lda + k0) * 2);
-        const uint32_t sb = (uint32_t)((BT ? (int64_t)n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + n0) * 2);
-        da.issue(lds + buf * C::STAGE, ra, sa, wave);
-        db.issue(lds + buf * C::STAGE + C::SA, rb, sb, wave);
+        return (uint32_t)((AT ? (int64_t)k0 * p.lda + m0 : (int64_t)m0 * p.lda + k0) * 2);
+    };
+    auto b_off = [&](int s) __attribute__((always_inline)) {
+        const int k0 = s * BK;
+        return (uint32_t)((BT ? (int64_t)n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + n0) * 2);
+    };
+    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
+        da.issue(lds + buf * C::STAGE, ra, a_off(s), wave);
+        db.issue(lds + buf * C::STAGE + C::SA, rb, b_off(s), wave);
     };
 
     // ---- per-lane LDS read addresses (stage 0, the wavefront's first chunk)
@@ -238,21 +243,29 @@ proj_gemm_bf16(GemmArgs p) {
     };
     int buf = 0;
     const int nfull = p.K / BK;  // steps wholly inside the contraction
-    for (int s = 0; s < nk; ++s) {
+    // One step.  MORE: a later step's loads are issued during it, a few after
+    // every TM products: issued in one go (200 .. 400 cycles for 4 .. 8 of them)
+    // they hold the wavefront's products up, between the products they cost
+    // little.  With two stages they must land within this very step, so they go
+    // into its first half; and where both operands take twice as many LDS reads
+    // besides (AT, not BT) the late loads cost 2 .. 5% more than they save, so they
+    // still go out in one go after the first reads.  In one go -> spread (us): dX 512
+    // x 2048 from 8192 29.5 -> 25.7, Y 4096 x 3072 from 2048 56.8 -> 54.2, dW 2048 x
+    // 3072 from 4096 65.0 -> 57.3, Y 1000 x 2304 from 768 9.2 -> 8.9; the tiles of one
+    // workgroup per CU gain most (tile 5 dX 1.2x, 12 dX 1.15x, 17 .. 20 dX 1.1 .. 1.2x).
+    // A step of two groups of products has nothing to spread them over (tile 16:
+    // dX 3768 x 64 from 3648 11.0 -> 12.1), and one loop is the smaller kernel where
+    // there is a single step (tile 3: U 512 x 2048 from 16 3.4 against 3.7).
+    constexpr bool SPREAD = KCW * TN >= 4 && !(NS == 2 && AT && !BT);
+    auto step = [&](auto more_c, int s) __attribute__((always_inline)) {
+        constexpr bool MORE = decltype(more_c)::value;
         wait_step(s);
         __syncthreads();
         const uint32_t stage = (uint32_t)buf * C::STAGE;
-        if (s == nfull) {  // the partial last step (every load of it has landed: nothing is in flight)
+        if (!(SPREAD && MORE) && s == nfull) {  // the partial last step (every load of it has landed: nothing is in flight)
             zero_tail(stage, p.K - s * BK);
             __syncthreads();
         }
-        // The first chunk's LDS reads go out before the next loads: their
-        // latency passes under the issue of those (an issue of 4 .. 8 loads takes
-        // a wavefront 200 .. 400 cycles, a 32 x 32 x 128 step about 500 in all).
-        // 3 .. 8% on the small tiles: X A 512 x 16 from 2048 6.2 -> 5.9 us, 1000 x
-        // 2304 from 768 9.9 -> 9.4; nothing on the large ones.  More stages in LDS
-        // (8 instead of 3) where a CU has one workgroup made it slower (6.2 -> 7.2
-        // us): the loads' issue bounds a step, not their latency.
         Frag<bf16> fa[2][TM], fb[2][TN];
         auto read = [&](auto j_c) __attribute__((always_inline)) {
             constexpr int J = decltype(j_c)::value;
@@ -261,18 +274,42 @@ proj_gemm_bf16(GemmArgs p) {
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) fb[J & 1][tn] = frag_b(stage, tn, J);
         };
+        const int later = buf == 0 ? NS - 1 : buf - 1;  // the stage step s - 1 used
+        const uint32_t sa = SPREAD && MORE ? a_off(s + NS - 1) : 0u, sb = SPREAD && MORE ? b_off(s + NS - 1) : 0u;
+        const uint32_t into = lds + (uint32_t)later * C::STAGE;
         read(std::integral_constant<int, 0>{});
-        if (s + NS - 1 < nk) issue(s + NS - 1, buf == 0 ? NS - 1 : buf - 1);
+        if constexpr (!SPREAD) {
+            if (s + NS - 1 < nk) issue(s + NS - 1, later);
+        }
         unroll_steps(std::make_integer_sequence<int, KCW>{}, [&](auto j_c) __attribute__((always_inline)) {
             constexpr int J = decltype(j_c)::value;
             if constexpr (J + 1 < KCW) read(std::integral_constant<int, J + 1>{});
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
+            for (int tn = 0; tn < TN; ++tn) {
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) mma(acc[tn][tm], fb[J & 1][tn], fa[J & 1][tm]);
+                if constexpr (MORE && SPREAD) {
+                    constexpr int GROUPS = NS == 2 ? (KCW * TN + 1) / 2 : KCW * TN, LA = TA::Dma::PER_WAVE;
+                    const int gi = J * TN + tn;
+                    if (gi < GROUPS) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int l = gi * C::LOADS / GROUPS; l < (gi + 1) * C::LOADS / GROUPS && l < C::LOADS; ++l) {
+                        if (l < LA)
+                            dma16<true>(ra, into + (uint32_t)(l * C::NW + wave) * 1024u, da.voff[l < LA ? l : 0], sa);
+                        else
+                            dma16<true>(rb, into + C::SA + (uint32_t)((l - LA) * C::NW + wave) * 1024u,
+                                        db.voff[l < LA ? 0 : l - LA], sb);
+                    }
+                    if (gi < GROUPS) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         });
         buf = buf + 1 == NS ? 0 : buf + 1;
-    }
+    };
+    int s = 0;
+    if constexpr (SPREAD)
+        for (; s < nk - (NS - 1); ++s) step(std::true_type{}, s);
+    for (; s < nk; ++s) step(std::false_type{}, s);
 
     if constexpr (WK > 1) {
         // Partial sums: wavefront (wm, wn, wk > 0) parks its accumulators in LDS
