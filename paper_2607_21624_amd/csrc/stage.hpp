@@ -33,10 +33,13 @@ struct TileGeom {
     static constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
     static constexpr int CPR = D / EPC;              // chunks per row
 
-    // Chunk XOR of row r (values < CPR).
+    // Chunk XOR of row r (values < CPR).  Rows of 256 bf16 (the projections' 256-wide
+    // tiles) need the rows of a transposed read apart like those of 128: on the
+    // narrow rule their four rows met in the same banks (tile 20 Y 1.1 .. 1.2x, tiles 11,
+    // 17, 19, 20 dW 1.05 .. 1.19x without; dW 4096 x 12288 from 4096 384 -> 349 us).
     static FBL_DEV int swz(int r) {
         if constexpr (sizeof(T) == 2) {
-            if constexpr (CPR == 16) return ((r & 3) << 2) | ((r >> 2) & 3);
+            if constexpr (CPR >= 16) return ((r & 3) << 2) | ((r >> 2) & 3);
             else if constexpr (CPR == 8) return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
             else return (r >> 2) & 3;
         } else {
