@@ -266,6 +266,15 @@ FBL_DEV void col_product(f32x16* acc, const StreamLane<T, D>& la, uint32_t off, 
     }
 }
 
+// v_mul_legacy_f32: 0 times anything is 0.  (The compiler has no builtin of this name; the
+// intrinsic lets it place the wait states.)
+extern "C" __device__ float mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+
+// dS = p (dP - D), and 0 where p is: a masked key's V row may hold anything finite, and its
+// dP then be inf or nan.  A second select instead of the product costs registers (B8 S128
+// H12 d64 bf16 8.8 -> 9.3 us); this one costs nothing at d = 32 and 64, 3% at 128.
+FBL_DEV float masked_ds(float p, float x) { return mul_legacy(p, x); }
+
 // Partial results through LDS: slot w holds one wavefront's 32 x D result as
 // [quad][lane] x 16 bytes.
 template <typename T, int D>
@@ -557,7 +566,7 @@ FBL_DEV void kv_pass(const BwdArgs& a, int id, unsigned char* kv_smem) {
                 float p = fast_exp2(__builtin_fmaf(s[r], a.scale_log2, -l4[e]));
                 if (acc_row(r, g) < row_min) p = 0.f;
                 s[r] = p;
-                dp[r] = p * (dp[r] - d4[e]);
+                dp[r] = masked_ds(p, dp[r] - d4[e]);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -592,6 +601,7 @@ FBL_DEV void kv_pass(const BwdArgs& a, int id, unsigned char* kv_smem) {
 #pragma unroll
             for (int w = 0; w < C::NS; ++w) x += parked<T, D>(kv_smem, slot + w, q, ln);
             x *= f;
+            if (own_key >= kv_end) x = f32x4{};  // no part in the sums, whatever dO and Q hold
             store4(row + 32 * (q / 4) + 8 * (q % 4) + 4 * (ln >> 5), x[0], x[1], x[2], x[3]);
         }
     };
@@ -685,7 +695,7 @@ FBL_DEV void q_pass(const BwdArgs& a, int id, unsigned char* q_smem) {
         for (int r = 0; r < 16; ++r) {
             float p = fast_exp2(__builtin_fmaf(s[r], a.scale_log2, -lse2));
             if (acc_row(r, g) >= row_end) p = 0.f;
-            dp[r] = p * (dp[r] - drow);
+            dp[r] = masked_ds(p, dp[r] - drow);
         }
         col_product<T, D>(dq, la, 0, dp);
         wait_lds();

@@ -87,3 +87,47 @@ def test_streams_rows_past_the_end_do_not_leak():
         torch.cuda.synchronize()
         for got, ref in zip((o, lse) + tuple(res), (plain[3], lse) + tuple(want)):
             assert torch.isfinite(got).all() and torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("dt", ["bfloat16", "float32"])
+def test_streams_masked_rows_may_hold_anything_finite(dt, d):
+    """Key padding over values so large that the masked scores and dP overflow
+    to inf and nan: every result is that of zeros in their place, and the masked
+    keys' gradients are zeros, also where dO is nan.  A causal pair (query 0, key
+    100) whose dP overflows reaches no gradient either."""
+    import torch
+    import paper_2607_21624_amd as fbl
+    dt = getattr(torch, dt)
+    B, S, H = 2, 161, 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, k, v, do = (torch.randn(B, S, H * d, generator=g, device="cuda").to(dt) for _ in range(4))
+    lens = torch.tensor([141, 40], dtype=torch.int32, device="cuda")
+    big, zero = [], []
+    for t, x in ((k, 1e30), (v, 3e38)):
+        big.append(t.clone())
+        zero.append(t.clone())
+        for b in range(B):
+            big[-1][b, lens[b]:] = x
+            zero[-1][b, lens[b]:] = 0
+    note(f"masked rows {dt} d={d}")
+
+    def run(k, v, do=do, kv_len=lens, causal=False):
+        o, lse = fbl.attn_fwd(q, k, v, H, H, causal=causal, kv_len=kv_len)
+        r = (o, lse) + fbl.attn_bwd(q, k, v, o, do, lse, H, H, causal=causal, kv_len=kv_len)
+        torch.cuda.synchronize()
+        return r
+
+    got, want = run(*big), run(*zero)
+    for a, b in zip(got, want):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+    bad = do.clone()
+    bad[:, 7] = float("nan")
+    for name, t in zip(("dk", "dv"), run(*big, do=bad)[3:]):
+        for b in range(B):
+            assert (t[b, lens[b]:] == 0).all(), name
+    far, wide = do.clone(), v.clone()
+    far[:, 0], wide[:, 100] = 1e20, 1e20  # their product is past the fp32 range; every allowed pair's is not
+    for t in run(k, wide, do=far, kv_len=None, causal=True):
+        assert torch.isfinite(t).all()
