@@ -324,9 +324,14 @@ PyObject* proj(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t M = x->size(0);
     const int64_t K = op == FBL_PROJ_BWD_DATA ? y->size(0) : x->size(1);
     const int64_t N = op == FBL_PROJ_BWD_DATA ? x->size(1) : y->size(1);
+    // the extent that both operands state, and the result's shape: the library checks neither
+    const int64_t orows = op == FBL_PROJ_BWD_WEIGHT ? K : M, ocols = op == FBL_PROJ_BWD_DATA ? K : N;
+    if (op == FBL_PROJ_FWD ? y->size(0) != K : op == FBL_PROJ_BWD_DATA ? y->size(1) != N : y->size(0) != M)
+        Py_RETURN_NONE;
+    if (out && (out->size(0) != orows || out->size(1) != ocols)) Py_RETURN_NONE;
     Tensor made;
     if (!out) {
-        made = empty({op == FBL_PROJ_BWD_WEIGHT ? K : M, op == FBL_PROJ_BWD_DATA ? K : N}, x->scalar_type(), *x);
+        made = empty({orows, ocols}, x->scalar_type(), *x);
         out = &made;
     }
     void *s = g.stream(), *px = x->data_ptr(), *py = y->data_ptr(), *pc = out->data_ptr();

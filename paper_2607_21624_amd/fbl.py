@@ -662,15 +662,22 @@ def _rows(t, name):
     return t.shape[0], t.shape[1], t.stride(0)
 
 
-def _proj_shape(op, a, b):
+def _proj_shape(op, a, b, out=None):
+    """(M, K, N, result shape, lda, ldb) of a product.  Both operands state one of its
+    extents and `out`, where given, has the result's shape: the library takes addresses
+    and extents alone, so what disagrees here would be read or written past its end."""
     ra, wa, lda = _rows(a, "a")
     rb, wb, ldb = _rows(b, "b")
     if op == FBL_PROJ_FWD:
-        M, K, N, shape = ra, wa, wb, (ra, wb)
+        M, K, N, shape, other = ra, wa, wb, (ra, wb), rb == wa
     elif op == FBL_PROJ_BWD_DATA:
-        M, N, K, shape = ra, wa, rb, (ra, rb)
+        M, N, K, shape, other = ra, wa, rb, (ra, rb), wb == wa
     else:
-        M, K, N, shape = ra, wa, wb, (wa, wb)
+        M, K, N, shape, other = ra, wa, wb, (wa, wb), rb == ra
+    if not other:
+        raise FblError(FBL_ERR_SHAPE, f"proj: operands {(ra, wa)} and {(rb, wb)} do not agree for op {op}")
+    if out is not None and tuple(out.shape) != shape:
+        raise FblError(FBL_ERR_SHAPE, f"proj: out has shape {tuple(out.shape)}, the result is {shape}")
     return M, K, N, shape, lda, ldb
 
 
@@ -684,7 +691,7 @@ def proj(op: int, a, b, out=None, tile: int = FBL_GEMM_TILE_AUTO, stream=None):
         return done
     import torch
     _check_device("proj", stream, a=a, b=b, out=out)
-    M, K, N, shape, lda, ldb = _proj_shape(op, a, b)
+    M, K, N, shape, lda, ldb = _proj_shape(op, a, b, out)
     if out is None:
         out = torch.empty(shape, dtype=a.dtype, device=a.device)
     _, _, ldc = _rows(out, "out")
@@ -723,7 +730,7 @@ def proj_tune(op: int, a, b, out, objective: int = FBL_TUNE_TIME, reps: int = 10
     (chosen id, {id: average ms} over the candidates); `out` then holds the
     product computed with the chosen tile."""
     _check_device("proj_tune", stream, a=a, b=b, out=out)
-    M, K, N, _, lda, ldb = _proj_shape(op, a, b)
+    M, K, N, _, lda, ldb = _proj_shape(op, a, b, out)
     _, _, ldc = _rows(out, "out")
     cap = LIB.fbl_gemm_tile_count()
     ms = (ctypes.c_float * cap)()

@@ -692,3 +692,27 @@ def test_bwd_launch_counts():
     l48 = fbl.fbl_layout_desc(BF16, 1, 64, 2, 48)
     assert F.LIB.fbl_attn_bwd_launches(ALL, ctypes.byref(l48), ctypes.byref(l48), 0, 1 << 20, -1, -1,
                                        ctypes.byref(n)) == F.FBL_ERR_UNSUPPORTED
+
+
+def test_proj_operand_shapes_agree():
+    """The extent that both operands of a projection product state agrees, and a
+    given output has the result's shape: refused in the binding, before the library
+    (which sees addresses and extents alone) could read or write past an end."""
+    import torch
+    t = lambda *s: torch.empty(s, dtype=torch.bfloat16)
+    M, K, N = 16, 24, 32
+    x, w, dy = t(M, K), t(K, N), t(M, N)
+    ops = {F.FBL_PROJ_FWD: (x, w, (M, N)), F.FBL_PROJ_BWD_DATA: (dy, w, (M, K)), F.FBL_PROJ_BWD_WEIGHT: (x, dy, (K, N))}
+    for op, (a, b, shape) in ops.items():
+        assert F._proj_shape(op, a, b)[:4] == (M, K, N, shape)
+        assert F._proj_shape(op, a, b, t(*shape))[:4] == (M, K, N, shape)
+        shared = 1 if op == F.FBL_PROJ_BWD_DATA else 0
+        for by in (-8, 8):
+            size = list(b.shape)
+            size[shared] += by
+            bad = [(a, t(*size), None), (a, b, t(shape[0] + by, shape[1])), (a, b, t(shape[0], shape[1] + by)),
+                   (a, b, t(shape[0] * shape[1]))]
+            for args in bad:
+                with pytest.raises(F.FblError) as e:
+                    F._proj_shape(op, *args)
+                assert e.value.status == F.FBL_ERR_SHAPE

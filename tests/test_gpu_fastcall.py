@@ -126,6 +126,18 @@ def test_other_calls_go_to_the_general_path(monkeypatch):
     for bad in ((3, x, x, None, -1, None), (0, x.half(), x, None, -1, None), (0, x.t(), x, None, -1, None),
                 (0, x, x.float(), None, -1, None), (0, x, x, x, -1, None), (0, x, x.cpu(), None, -1, None)):
         assert F.proj(*bad) is None
+    e = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda")
+    X, W, dY = e(32, 64), e(64, 96), e(32, 96)  # operands that disagree, outputs of another shape: refused by both
+    for bad in ((0, X, W[:56], None), (0, X, e(72, 96), None), (1, dY, W[:, :88], None), (1, dY[:, :88], W, None),
+                (2, X, dY[:24], None), (2, X[:24], dY, None), (0, X, W, e(31, 96)), (0, X, W, e(33, 96)),
+                (0, X, W, e(32, 104)), (1, dY, W, e(32, 72)), (2, X, dY, e(56, 96))):
+        assert F.proj(*bad, -1, None) is None
+        with pytest.raises(fbl.FblError) as err:
+            fbl.proj(*bad)
+        assert err.value.status == fbl.FBL_ERR_SHAPE
+        if bad[3] is not None:
+            with pytest.raises(fbl.FblError):
+                fbl.proj_tune(*bad)
     with pytest.raises(fbl.FblError):
         fbl.attn_fwd(q, k, v, 2, 2, tile=99)
     with torch.cuda.stream(torch.cuda.Stream()):  # the current stream, whichever it is
