@@ -579,6 +579,15 @@ void fbl_proj_tune_reset(void);
  */
 fbl_status fbl_proj_auto_tile(uint32_t op, int64_t M, int64_t K, int64_t N, int32_t* tile);
 
+/*
+ * The tile that an fp32 product (op, M, K, N) of fbl_proj_dt runs, chosen from
+ * the shape: info[0..5] = output rows and columns of a workgroup, contraction
+ * depth of a step, wavefronts, how many of them share a step's contraction, and
+ * workgroups launched.  Pure host function.
+ * FBL_ERR_NULL, FBL_ERR_ARG (unknown op) or FBL_ERR_SHAPE on bad arguments.
+ */
+fbl_status fbl_proj_float_tile(uint32_t op, int64_t M, int64_t K, int64_t N, int32_t* info);
+
 /* Static, human-readable name of a status code. */
 const char* fbl_status_str(fbl_status s);
 

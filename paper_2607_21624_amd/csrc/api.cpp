@@ -1277,6 +1277,19 @@ fbl_status fbl_proj_auto_tile(uint32_t op, int64_t M, int64_t K, int64_t N, int3
     return FBL_OK;
 }
 
+fbl_status fbl_proj_float_tile(uint32_t op, int64_t M, int64_t K, int64_t N, int32_t* info) {
+    if (!info) return FBL_ERR_NULL;
+    if (op > FBL_PROJ_BWD_WEIGHT) return FBL_ERR_ARG;
+    if (M <= 0 || K <= 0 || N <= 0 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX) return FBL_ERR_SHAPE;
+    ProjPlan pl;
+    proj_shape(op, M, K, N, pl);
+    pl.p.M = (int)pl.orows;
+    pl.p.N = (int)pl.ocols;
+    pl.p.K = (int)pl.kc;
+    fbl::proj_gemm_f32_info(pl.p, info);
+    return FBL_OK;
+}
+
 void fbl_proj_tune_reset(void) {
     std::lock_guard<std::mutex> lock(g_tuned_mu);
     g_tuned.clear();

@@ -81,6 +81,8 @@ hipError_t launch_attn_bwd_dq_bf16(const BwdArgs& a, int tile, hipStream_t strea
 hipError_t launch_proj_gemm(int a_kmajor, int b_nmajor, int tile, const GemmArgs& p, hipStream_t stream);
 // The same products for fp32 storage (proj_gemm_f32.hip); the tile follows from the shape.
 hipError_t launch_proj_gemm_f32(int a_kmajor, int b_nmajor, const GemmArgs& p, hipStream_t stream);
+// That tile (bm, bn, bk, wavefronts, wk) and the workgroups it takes, for an M x N output.
+void proj_gemm_f32_info(const GemmArgs& p, int32_t* info);
 
 // Diagnostic: offsets of a token-major tensor computed by the device index map.
 hipError_t launch_layout_map(const TokMap& m, int B, int H, int S, int D, int64_t* out, hipStream_t stream);

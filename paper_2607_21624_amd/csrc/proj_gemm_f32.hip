@@ -15,6 +15,7 @@
 // wavefronts split the contraction.  512 tokens x 768 x 3072: Y 112 -> 26, dX
 // 336 -> 30, dW 91 -> 28 us (82 .. 94 TFLOP/s) against 64 x 64 tiles staged by
 // single floats; 4096 x 2048 x 2048 252 .. 293 us (117 .. 136 TFLOP/s).
+#include <algorithm>
 #include <array>
 #include <utility>
 
@@ -102,6 +103,11 @@ struct FTile {
         }
     }
 };
+
+// Workgroups of a product: whole groups of 8, one per XCD (xcd_logical_id).
+int64_t f32_workgroups(const F32Tile& t, const GemmArgs& p) {
+    return ((((int64_t)p.M + t.bm - 1) / t.bm) * (((int64_t)p.N + t.bn - 1) / t.bn) + 7) / 8 * 8;
+}
 
 // AT: A stored k-major ([K, M] rows); BT: B stored n-major ([N, K] rows).
 template <int I, bool AT, bool BT>
@@ -244,8 +250,7 @@ hipError_t launch_id(const GemmArgs& p, hipStream_t stream) {
     constexpr auto kernel = &proj_gemm_f32<I, AT, BT>;
     const hipError_t once = ensure_dynamic_lds<kernel>(C::BYTES);
     if (once != hipSuccess) return once;
-    const int tiles = ((p.M + C::t.bm - 1) / C::t.bm) * ((p.N + C::t.bn - 1) / C::t.bn);
-    hipLaunchKernelGGL(kernel, dim3((tiles + 7) / 8 * 8), dim3(C::NT), C::BYTES, stream, p);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)f32_workgroups(C::t, p)), dim3(C::NT), C::BYTES, stream, p);
     return hipGetLastError();
 }
 
@@ -272,19 +277,21 @@ hipError_t launch_tile(int tile, const GemmArgs& p, hipStream_t stream) {
 // / 179 for tiles 0 .. 4; the picks are within 10% of the best of each).  Few
 // small tiles with a deep contraction split it over 8 wavefronts: 33 x 2048
 // from 2048 17.6 -> 16.0 us, 128 x 768 from 3072 25.2 -> 22.2 us.
+// A launch holds less than 2^32 threads: a 2 GB column of outputs (2^29 rows of
+// one) has too many 32-row tiles for it.
 int f32_tile(const GemmArgs& p) {
     constexpr double kCost[5][2] = {{3.5, 3.0}, {4.0, 3.2}, {4.7, 3.6}, {4.8, 4.1}, {5.2, 4.4}};  // one round, more
     int best = 0;
     double best_cost = 0;
     for (int i = 0; i < 5; ++i) {
         const F32Tile& t = kF32Tiles[i];
-        const int64_t tiles = (int64_t)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
+        const int64_t tiles = f32_workgroups(t, p);
+        if (i > 0 && tiles * 256 > UINT32_MAX) break;
         const int64_t rounds = (tiles + 255) / 256;
         const double cost = (double)rounds * (t.bm * t.bn) * kCost[i][rounds > 1];
         if (i == 0 || cost < best_cost) best = i, best_cost = cost;
     }
-    const int64_t n32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
-    return best == 4 && n32 <= 256 && p.K >= 768 ? 5 : best;
+    return best == 4 && f32_workgroups(kF32Tiles[4], p) <= 256 && p.K >= 768 ? 5 : best;
 }
 
 hipError_t launch_f32(int a_kmajor, int b_nmajor, int tile, const GemmArgs& p, hipStream_t stream) {
@@ -297,6 +304,13 @@ hipError_t launch_f32(int a_kmajor, int b_nmajor, int tile, const GemmArgs& p, h
 
 hipError_t launch_proj_gemm_f32(int a_kmajor, int b_nmajor, const GemmArgs& p, hipStream_t stream) {
     return launch_f32(a_kmajor, b_nmajor, f32_tile(p), p, stream);
+}
+
+void proj_gemm_f32_info(const GemmArgs& p, int32_t* info) {
+    const F32Tile& t = kF32Tiles[f32_tile(p)];
+    const int32_t v[6] = {t.bm, t.bn, t.bk, t.wm * t.wn * t.wk, t.wk,
+                          (int32_t)std::min<int64_t>(f32_workgroups(t, p), INT32_MAX)};
+    for (int i = 0; i < 6; ++i) info[i] = v[i];
 }
 
 }  // namespace fbl

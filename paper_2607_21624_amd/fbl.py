@@ -58,7 +58,7 @@ EXPORTED = ("fbl_layout_desc", "fbl_layout_packed_qkv", "fbl_layout_offset", "fb
             "fbl_attn_tile_info", "fbl_attn_candidates", "fbl_attn_auto_tiles", "fbl_attn_tune", "fbl_attn_tuned_tile",
             "fbl_attn_tune_reset", "fbl_proj", "fbl_proj_dt",
             "fbl_gemm_tile_count", "fbl_gemm_tile_info", "fbl_proj_candidates", "fbl_proj_tune", "fbl_proj_tuned_tile", "fbl_proj_auto_tile",
-            "fbl_proj_tune_reset", "fbl_status_str")
+            "fbl_proj_float_tile", "fbl_proj_tune_reset", "fbl_status_str")
 
 
 class Layout(ctypes.Structure):
@@ -167,6 +167,8 @@ def _load() -> ctypes.CDLL:
     lib.fbl_proj_tuned_tile.restype = ctypes.c_int32
     lib.fbl_proj_auto_tile.argtypes = [ctypes.c_uint32] + [ctypes.c_int64] * 3 + [ctypes.POINTER(ctypes.c_int32)]
     lib.fbl_proj_auto_tile.restype = ctypes.c_int
+    lib.fbl_proj_float_tile.argtypes = [ctypes.c_uint32] + [ctypes.c_int64] * 3 + [ctypes.POINTER(ctypes.c_int32)]
+    lib.fbl_proj_float_tile.restype = ctypes.c_int
     lib.fbl_proj_tune_reset.argtypes = []
     lib.fbl_proj_tune_reset.restype = None
     lib.fbl_status_str.argtypes = [ctypes.c_int]
@@ -750,6 +752,13 @@ def proj_auto_tile(op: int, M: int, K: int, N: int) -> int:
     t = ctypes.c_int32(-1)
     _check(LIB.fbl_proj_auto_tile(op, M, K, N, ctypes.byref(t)), "fbl_proj_auto_tile")
     return t.value
+
+
+def proj_float_tile(op: int, M: int, K: int, N: int):
+    """The tile an fp32 product runs: dict(bm, bn, bk, waves, wk, workgroups)."""
+    info = (ctypes.c_int32 * 6)()
+    _check(LIB.fbl_proj_float_tile(op, M, K, N, info), "fbl_proj_float_tile")
+    return dict(zip(("bm", "bn", "bk", "waves", "wk", "workgroups"), list(info)))
 
 
 def proj_tune_reset() -> None:

@@ -716,3 +716,20 @@ def test_proj_operand_shapes_agree():
                 with pytest.raises(F.FblError) as e:
                     F._proj_shape(op, *args)
                 assert e.value.status == F.FBL_ERR_SHAPE
+
+
+def test_proj_f32_tiles_fit_a_launch():
+    """An fp32 product's tile keeps its grid below 2^32 threads, also for a 2 GB
+    column or row of outputs, whose 32-row tiles alone would not."""
+    FWD, BD, BW = F.FBL_PROJ_FWD, F.FBL_PROJ_BWD_DATA, F.FBL_PROJ_BWD_WEIGHT
+    n = 2 ** 29 - 1
+    for op, M, K, N in ((FWD, n, 1, 1), (FWD, 1, 1, n), (BD, n, 1, 1), (BD, 1, n, 1), (BW, 1, n, 1), (BW, 1, 1, n),
+                        (FWD, n - 512, 1, 1), (FWD, 22000, 1, 22000), (FWD, 1, n, 1)):
+        t = fbl.proj_float_tile(op, M, K, N)
+        assert t["workgroups"] * 64 * t["waves"] < 2 ** 32, (op, M, K, N, t)
+        rows, cols = {FWD: (M, N), BD: (M, K), BW: (K, N)}[op]
+        assert t["workgroups"] >= -(-rows // t["bm"]) * -(-cols // t["bn"])
+    info = (ctypes.c_int32 * 6)()
+    assert fbl.LIB.fbl_proj_float_tile(FWD, 64, 64, 64, None) == F.FBL_ERR_NULL
+    assert fbl.LIB.fbl_proj_float_tile(3, 64, 64, 64, info) == F.FBL_ERR_ARG
+    assert fbl.LIB.fbl_proj_float_tile(FWD, 0, 64, 64, info) == F.FBL_ERR_SHAPE
