@@ -252,16 +252,29 @@ def test_proj_fp32_matches_oracle(M, K, N):
         assert rel_err(to_np(view), ref) <= 1e-4, f"op {op}"
 
 
-@pytest.mark.parametrize("M,K,N", [(4000, 24, 2040), (2100, 20, 4100), (1290, 52, 2050), (1020, 33, 1000),
-                                   (129, 70, 333), (45, 803, 77), (1, 769, 1)])
-def test_proj_fp32_every_tile(M, K, N):
+F32_TILES = {(128, 128, 1): (4000, 24, 2040), (128, 64, 1): (2100, 20, 4100), (64, 64, 1): (1290, 52, 2050),
+             (64, 32, 2): (1020, 33, 1000), (32, 32, 4): (129, 70, 333), (32, 32, 8): (45, 803, 77)}
+F32_CASES = [(t, op, s) for t, s in F32_TILES.items() for op in range(3)] + [((32, 32, 8), op, (1, 769, 1)) for op in range(3)]
+
+
+def _f32_extents(op, rows, kc, cols):
+    """(M, K, N) of the product of kind `op` with a rows x cols output and contraction kc."""
+    return {0: (rows, kc, cols), 1: (rows, cols, kc), 2: (kc, rows, cols)}[op]
+
+
+@pytest.mark.parametrize("tile,op,shape", F32_CASES)
+def test_proj_fp32_every_tile(tile, op, shape):
     """Each fp32 tile (128x128 ... 32x32, the contraction split over 1, 2, 4 and
-    8 wavefronts) on ragged extents: operands are column views of wider buffers
+    8 wavefronts) in each of the three products' operand orientations, on ragged
+    extents: operands are column views of wider buffers
     at an odd 4-byte offset whose other columns and following rows are NaN, so a
     read past an extent that reaches a result shows.  Each result is within the
     bound of a K-term fp32 sum in any order, (K + 2) 2^-24 sum |a||b|."""
     import torch
     fbl = _lib()
+    M, K, N = _f32_extents(op, *shape)
+    t = fbl.proj_float_tile(op, M, K, N)
+    assert (t["bm"], t["bn"], t["wk"]) == tile, "the shape no longer runs the tile it is here for"
     rng = np.random.default_rng(M + 5 * K + 11 * N)
 
     def wide(x):
@@ -271,18 +284,16 @@ def test_proj_fp32_every_tile(M, K, N):
         return view
 
     x, w, dy = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
-    X, W, dY = wide(x), wide(w), wide(dy)
-    note(f"proj fp32 tiles M={M} K={K} N={N}")
-    for op, a, b, fa, fb in ((fbl.FBL_PROJ_FWD, X, W, x, w), (fbl.FBL_PROJ_BWD_DATA, dY, W, dy, w.T),
-                             (fbl.FBL_PROJ_BWD_WEIGHT, X, dY, x.T, dy)):
-        ref = fa.astype(np.float64) @ fb.astype(np.float64)
-        bound = (fa.shape[1] + 2) * 2.0 ** -24 * (np.abs(fa).astype(np.float64) @ np.abs(fb).astype(np.float64))
-        out = torch.full((ref.shape[0] + 1, ref.shape[1] + 3), float("nan"), dtype=torch.float32, device="cuda")
-        view = out[:ref.shape[0], :ref.shape[1]]
-        fbl.proj(op, a, b, out=view)
-        torch.cuda.synchronize()
-        assert torch.isnan(out[ref.shape[0]:]).all() and torch.isnan(out[:, ref.shape[1]:]).all(), f"op {op}: outside"
-        assert (np.abs(to_np(view) - ref) <= bound).all(), f"op {op}"
+    note(f"proj fp32 tile {tile} op={op} M={M} K={K} N={N}")
+    a, b, fa, fb = {0: (x, w, x, w), 1: (dy, w, dy, w.T), 2: (x, dy, x.T, dy)}[op]
+    ref = fa.astype(np.float64) @ fb.astype(np.float64)
+    bound = (fa.shape[1] + 2) * 2.0 ** -24 * (np.abs(fa).astype(np.float64) @ np.abs(fb).astype(np.float64))
+    out = torch.full((ref.shape[0] + 1, ref.shape[1] + 3), float("nan"), dtype=torch.float32, device="cuda")
+    view = out[:ref.shape[0], :ref.shape[1]]
+    fbl.proj(op, wide(a), wide(b), out=view)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[ref.shape[0]:]).all() and torch.isnan(out[:, ref.shape[1]:]).all(), "outside"
+    assert (np.abs(to_np(view) - ref) <= bound).all()
 
 
 @pytest.mark.parametrize("op,M,K,N", [(0, 512, 2048, 8192), (1, 512, 4096, 12288), (2, 512, 1024, 4096),
