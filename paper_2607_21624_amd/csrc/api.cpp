@@ -210,49 +210,6 @@ bool bwd_fuses(const fbl_layout* lq, const fbl_layout* lk) {
     return lq->B * lk->H >= 128 || blocks <= 64;
 }
 
-// Backward in one launch, 32 keys or 32 queries per workgroup.  Up to 128 keys it
-// stands beside the fused pass (bwd_fuses), which holds a pair's keys in one
-// workgroup: faster once the pairs alone fill the chip.  Measured (us, fused
-// -> 32 rows): bf16 d = 64 B8 H12 S128 (384 key blocks) 16.1 -> 9.3, B8 H32 S128
-// (1024) 14.6 -> 21.1; d = 128 H32 S128 (128) 22.7 -> 9.8, B8 (1024) 28 -> 61; fp32
-// d = 64 B4 H16 S128 (256) 38 -> 16, B16 (1024) 43 -> 53.
-bool streams_over_fused(const fbl_layout* lq, const fbl_layout* lk) {
-    return lq->B * lk->H * blocks32(lk->S) <= (lq->D == 128 ? 256 : 512);
-}
-
-// Beyond 128 keys, instead of statistics, key/value and dQ passes.  The three
-// launches share their tiles among four times the rows, and bf16 contracts a
-// stored dS; one launch of 32-row workgroups has no gaps and no long chains.
-// Both are modelled in us, fitted to 75 bf16 shapes of 129 .. 4096 keys (rms error 9
-// .. 16%); with the margin no shape measured got slower:
-//   one launch  start + max(step * query blocks of a kv group,
-//                           block * 32 x 32 blocks of scores + wg * workgroups)
-//   three       start + q * query blocks + block * blocks + group * min(group's, 40)
-// fp32 has no stored dS to lose: one launch at every size up to d = 64 (B2 H12
-// S500 causal 59 -> 45, B4 H16/4 S1024 causal 331 -> 269, B1 H16 S1024 129 -> 127);
-// at d = 128, one wavefront per SIMD, up to one workgroup per CU (H8 S256 50 ->
-// 27, B2 H8 S1024 172 -> 180).
-// (129 .. 135 keys keep three launches: their count there is documented.)
-bool bwd_streams(const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind) {
-    if (lk->S < 136) return false;
-    const int64_t nq = blocks32(lq->S), nk = blocks32(lk->S);
-    const double wgs = (double)(lq->B * lk->H * nk + lq->B * lq->H * nq);
-    if (lq->dtype != FBL_BF16) return lq->D <= 64 || wgs <= 256;
-    struct Cost { double start, step, block, wg, start3, q3, block3, group3; };
-    static const Cost costs[3] = {
-        {4.2, 0.271, 0.83e-3, 2.5e-3, 15.4, 0.439, 0.90e-3, 0.025},   // d = 32
-        {5.3, 0.402, 1.02e-3, 6.7e-3, 17.9, 0.445, 1.04e-3, 0.068},   // 64
-        {6.5, 0.691, 4.47e-3, 20.7e-3, 21.9, 0.303, 2.69e-3, 0.300},  // 128
-    };
-    const Cost& c = costs[lq->D == 32 ? 0 : lq->D == 64 ? 1 : 2];
-    double blocks = (double)(lq->B * lq->H) * (double)nq * (double)nk;
-    if (mask_kind & FBL_MASK_CAUSAL) blocks *= (double)(nq + 1) / (double)(2 * nq);
-    const double group = (double)(lq->H / lk->H) * (double)nq;
-    const double one = c.start + std::max(c.step * group, c.block * blocks + c.wg * wgs);
-    const double three = c.start3 + c.q3 * (double)nq + c.block3 * blocks + c.group3 * std::min(group, 40.0);
-    return one < 0.85 * three;
-}
-
 template <typename T>
 hipError_t dispatch_bwd(int D, const fbl::BwdArgs& a, unsigned phases, hipStream_t s) {
     switch (D) {
@@ -422,6 +379,144 @@ int kv_split_for(const fbl_layout* lq, const fbl_layout* lk, bool causal, int ti
            iters >= 16 * split)
         split *= 2;
     return split;
+}
+
+// Two bounds of which the larger decides, rounded where they meet.
+double larger(double a, double b) { return std::pow(a * a * a * a + b * b * b * b, 0.25); }
+
+// What decides between the backward's forms: the workgroups of the one-launch
+// form and the steps (32 x 32 blocks, four at a time) of its longest chains and,
+// on average, of a slot of the chip (its workgroups over those resident).
+struct StreamsWork {
+    double kv_chain, q_chain;  // steps of the longest key and query workgroups
+    double kv_steps, q_steps;  // steps per slot
+    double kv_wgs, q_wgs;      // workgroups per slot
+    StreamsWork(const fbl_layout* lq, const fbl_layout* lk, bool causal, int occ) {
+        const int64_t nq = blocks32(lq->S), nk = blocks32(lk->S), group = lq->H / lk->H * nq;
+        const double slots = 256.0 * occ, part = causal ? 0.5 * (1.0 + 1.0 / (double)nq) : 1.0;
+        kv_chain = (double)((group + 3) / 4);
+        q_chain = (double)((nk + 3) / 4);
+        kv_wgs = (double)(lq->B * lk->H * nk) / slots;
+        q_wgs = (double)(lq->B * lq->H * nq) / slots;
+        // (a workgroup's last step may leave streams idle)
+        kv_steps = kv_wgs * (causal ? (double)group * part / 4 + 0.375 : kv_chain);
+        q_steps = q_wgs * (causal ? (double)nk * part / 4 + 0.375 : q_chain);
+    }
+};
+
+// Backward in one launch, 32 keys or 32 queries per workgroup.  Up to 128 keys it
+// stands beside the fused pass (bwd_fuses), which holds a pair's keys in one
+// workgroup: faster once the pairs alone fill the chip.  Measured (us, fused
+// -> 32 rows): bf16 d = 64 B8 H12 S128 (384 key blocks) 16.1 -> 9.3, B8 H32 S128
+// (1024) 14.6 -> 21.1; d = 128 H32 S128 (128) 22.7 -> 9.8, B8 (1024) 28 -> 61; fp32
+// d = 64 B4 H16 S128 (256) 38 -> 16, B16 (1024) 43 -> 53.  Many queries on few keys make
+// it the slower one again, each of its query workgroups reading Q, dO and O for one
+// step: d = 64 B16 H16 4096 on 32 (256 pairs) 311 -> 388, but B5 H32/16 1618 on 42
+// (80) 244 -> 173 and B16 H8 8192 on 100 (128) 642 -> 512; d = 128 454 -> 1097, B8 H20
+// 185 on 31 26 -> 36.
+bool streams_over_fused(const fbl_layout* lq, const fbl_layout* lk, bool causal) {
+    const int64_t pairs = lq->B * lk->H, key_blocks = pairs * blocks32(lk->S);
+    if (lq->D == 128) {  // one workgroup per CU: modelled (us, 70 shapes, rms error 12%)
+        if (key_blocks > 256) return false;
+        const StreamsWork w(lq, lk, causal, 1);
+        const double blocks = (double)(lq->H / lk->H * blocks32(lq->S));
+        const double fused = (6.0 + 3.35 * blocks) * (1.0 + 1.19 * std::max(0.0, (double)pairs / 256 - 1.0));
+        const double bytes = (double)(lq->B * lq->S * lq->H * lq->D * 2);
+        const double one = 5.3 + larger(3.0 * w.kv_chain, 2.35 * w.kv_wgs * w.kv_chain + 3.9 * w.kv_wgs +
+                                                              4.3 * w.q_wgs + 1.5e-6 * bytes);
+        return one < fused;
+    }
+    const int64_t query_blocks = lq->B * lq->H * blocks32(lq->S);
+    // fp32, one or two query blocks a pair: the fused pass is done after as many steps (B6 H32
+    // S64 21.8 us, 768 workgroups of 32 rows 26.4; B27 H4 S35 20.2, 432 of them 14.2)
+    if (lq->dtype == FBL_F32 && lq->D == 64 && pairs <= 256 && lq->H / lk->H * blocks32(lq->S) <= 2)
+        return key_blocks + query_blocks <= 512;
+    return key_blocks <= 512 && !(lq->dtype == FBL_BF16 && lq->D == 64 && pairs >= 192 && query_blocks > 8 * 768);
+}
+
+// Beyond 128 keys, instead of statistics, key/value and dQ passes.  The three
+// launches share their tiles among four times the rows, and bf16 contracts a
+// stored dS; one launch of 32-row workgroups has no gaps and no long chains.
+// Both are modelled in us, fitted to 75 bf16 shapes of 129 .. 4096 keys (rms error 9
+// .. 16%), and one launch needs a margin:
+//   one launch  start + max(step * query blocks of a kv group,
+//                           block * 32 x 32 blocks of scores + wg * workgroups)
+//   three       start + q * query blocks + block * blocks + group * min(group's, 40)
+// What that leaves out -- many queries on few keys, the idle streams of a last
+// step, key workgroups that fill the chip before the first query workgroup, what
+// the split saves the kv pass -- let it pick one launch where that was up to twice as
+// slow (d = 64: 8192 queries on 200 keys, 2 heads, 56 -> 105 us; B2 S2048 H8 without a
+// mask 82 -> 99).  So streams_lose, fitted to 770 shapes, must agree.
+// fp32 has no stored dS to lose: one launch at every size up to d = 64 (B2 H12
+// S500 causal 59 -> 45, B4 H16/4 S1024 causal 331 -> 269, B1 H16 S4096 2019 -> 1843);
+// at d = 128, one wavefront per SIMD, up to one workgroup per CU (H8 S256 50 ->
+// 27, B2 H8 S1024 172 -> 180).
+// 129 .. 135 keys, and fp32 at d = 128 up to 135, keep their three launches although
+// one is faster (B8 H12 S130 bf16 d = 64 19.4 -> 12.2 us, B4 H16 S64 fp32 d = 128 33 ->
+// 17.5): callers may count on the launches fbl_attn_bwd_launches has always
+// reported next to the 128-key line, and tests do.
+bool streams_lose(const fbl_layout* lq, const fbl_layout* lk, bool causal, int kv_tile);
+
+bool bwd_streams(const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind, int kv_tile) {
+    if (lk->S < 136) return false;
+    const int64_t nq = blocks32(lq->S), nk = blocks32(lk->S);
+    const double wgs = (double)(lq->B * lk->H * nk + lq->B * lq->H * nq);
+    if (lq->dtype != FBL_BF16) return lq->D <= 64 || wgs <= 256;
+    struct Cost { double start, step, block, wg, start3, q3, block3, group3; };
+    static const Cost costs[3] = {
+        {4.2, 0.271, 0.83e-3, 2.5e-3, 15.4, 0.439, 0.90e-3, 0.025},   // d = 32
+        {5.3, 0.402, 1.02e-3, 6.7e-3, 17.9, 0.445, 1.04e-3, 0.068},   // 64
+        {6.5, 0.691, 4.47e-3, 20.7e-3, 21.9, 0.303, 2.69e-3, 0.300},  // 128
+    };
+    const Cost& c = costs[lq->D == 32 ? 0 : lq->D == 64 ? 1 : 2];
+    double blocks = (double)(lq->B * lq->H) * (double)nq * (double)nk;
+    if (mask_kind & FBL_MASK_CAUSAL) blocks *= (double)(nq + 1) / (double)(2 * nq);
+    const double group = (double)(lq->H / lk->H) * (double)nq;
+    const double one = c.start + std::max(c.step * group, c.block * blocks + c.wg * wgs);
+    const double three = c.start3 + c.q3 * (double)nq + c.block3 * blocks + c.group3 * std::min(group, 40.0);
+    return one < 0.85 * three && !streams_lose(lq, lk, (mask_kind & FBL_MASK_CAUSAL) != 0, kv_tile);
+}
+
+// bf16 beyond 128 keys: whether three launches take less time than one.  Modelled (us),
+// fitted to 770 shapes of 129 .. 16384 keys, 16 .. 16384 queries and groups of 1 .. 8
+// heads (rms error 7 .. 12%):
+//   one launch  start + the largest of its key workgroups' longest chain, its slots'
+//               work, and its query workgroups' chain behind the key workgroups
+//   three       start + kv pass (its longest workgroup, or the slots' work) + dQ
+//               pass (its key blocks in turn, or all blocks) + the split's reduction
+// Of those shapes 410 take one launch (463 without it); 7 of them are more than 3%
+// slower than with three (52 without): d = 32 H20/5 S6178 causal by 53%, one by 21%,
+// the rest by up to 11%.  Two were faster with one, by up to 10%.
+bool streams_lose(const fbl_layout* lq, const fbl_layout* lk, bool causal, int kv_tile) {
+    struct Cost {
+        int occ;
+        double start, kv_chain, q_chain, kv_step, q_step, kv_wg, q_wg;                     // one launch
+        double start3, kv3_iter, kv3_slot, kv3_wg, dq_key, dq_block, dq_row, split, part;  // three
+    };
+    static const Cost costs[3] = {
+        {3, 3.17, 1.086, 0.566, 2.46, 0.21, 1.25, 3.10, 12.9, 0.531, 0.615, 1.32, 0.318, 0.418, 1.14, 3.38, 2.97},
+        {3, 3.74, 1.666, 0.975, 1.03, 3.16, 3.61, 4.02, 15.3, 0.401, 0.310, 6.66, 0.420, 0.813, 3.16, 4.56, 0.76},
+        {1, 5.59, 2.841, 1.345, 3.69, 0.50, 3.20, 6.23, 16.1, 1.058, 1.108, 11.5, 0.432, 0.347, 4.57, 3.85, 1.21},
+    };
+    const Cost& c = costs[lq->D == 32 ? 0 : lq->D == 64 ? 1 : 2];
+    const int64_t nq = blocks32(lq->S), nk = blocks32(lk->S);
+    const double part = causal ? 0.5 * (1.0 + 1.0 / (double)nq) : 1.0;
+    const StreamsWork w(lq, lk, causal, c.occ);
+    const double kv_part = c.kv_step * w.kv_steps + c.kv_wg * w.kv_wgs;
+    const double q_from = w.kv_wgs > 1 ? kv_part * (1.0 - 1.0 / w.kv_wgs) : 0.0;
+    const double one = c.start + larger(larger(c.kv_chain * w.kv_chain, q_from + c.q_chain * w.q_chain),
+                                        kv_part + c.q_step * w.q_steps + c.q_wg * w.q_wgs);
+    const fbl::AttnTile& t = fbl::kAttnTiles[kv_tile];
+    const int split = kv_split_for(lq, lk, causal, kv_tile);
+    const double slots = 256.0 * fbl::attn_occ(t, (int)lq->D);
+    const double items = (double)(lq->B * lk->H * ((lk->S + fbl::attn_rows(t) - 1) / fbl::attn_rows(t)));
+    const double iters = (double)(lq->H / lk->H * ((lq->S + t.cols - 1) / t.cols)) * t.cols / 32.0;
+    const double kv = larger(c.kv3_iter * iters / split, c.kv3_slot * items * iters * part / slots +
+                                                             c.kv3_wg * items * split / slots);
+    const double rows = (double)(lq->B * lq->H * nq) * 1e-3;
+    const double dq = larger(c.dq_key * (double)nk, c.dq_block * rows * (double)nk * part + c.dq_row * rows);
+    const double sums = split > 1 ? c.split + c.part * (double)(lk->B * lk->S * lk->H * lk->D * split) * 1e-6 : 0;
+    return one >= 0.985 * (c.start3 + kv + dq + sums);
 }
 
 // Workspace, part 3 (with part 2 only): the split key/value pass's fp32
@@ -625,8 +720,9 @@ fbl_status bwd_plan(uint32_t phases, const fbl_layout* lq, const fbl_layout* lk,
     // the whole backward with automatic tiles: one launch up to 128 keys and, where
     // no tile has been measured for the shape, beyond them
     if (phases == FBL_BWD_ALL && kv_tile == FBL_ATTN_TILE_AUTO && dq_tile == FBL_ATTN_TILE_AUTO) {
-        if (bwd_fuses(lq, lk)) p->streams = streams_over_fused(lq, lk), p->fused = !p->streams;
-        else p->streams = !tuned[0] && !tuned[1] && bwd_streams(lq, lk, mask_kind);
+        const bool causal = (mask_kind & FBL_MASK_CAUSAL) != 0;
+        if (bwd_fuses(lq, lk)) p->streams = streams_over_fused(lq, lk, causal), p->fused = !p->streams;
+        else p->streams = !tuned[0] && !tuned[1] && bwd_streams(lq, lk, mask_kind, p->kv_tile);
     }
     // stored-dS path when the workspace holds the dS blocks, else recompute
     const size_t ds_bytes = ws_ds_bytes(lq, lk);

@@ -733,3 +733,20 @@ def test_proj_f32_tiles_fit_a_launch():
     assert fbl.LIB.fbl_proj_float_tile(FWD, 64, 64, 64, None) == F.FBL_ERR_NULL
     assert fbl.LIB.fbl_proj_float_tile(3, 64, 64, 64, info) == F.FBL_ERR_ARG
     assert fbl.LIB.fbl_proj_float_tile(FWD, 0, 64, 64, info) == F.FBL_ERR_SHAPE
+
+
+def test_one_launch_backward_where_it_is_the_faster():
+    """The automatic backward takes one launch on small and mid-sized bf16 calls,
+    and the three passes where they were measured faster: many queries on few keys,
+    and unmasked grids of key workgroups that fill the chip for long."""
+    def one(B, Sq, Skv, Hq, Hkv, D, mask):
+        lq, lk = fbl.fbl_layout_desc(BF16, B, Sq, Hq, D), fbl.fbl_layout_desc(BF16, B, Skv, Hkv, D)
+        return fbl.attn_bwd_launches(lq, lk, mask, fbl.fbl_attn_bwd_workspace(lq, lk)) == 1
+
+    for shape in ((1, 1024, 1024, 16, 16, 64, 1), (4, 448, 300, 20, 20, 64, 2), (2, 300, 300, 8, 8, 128, 1),
+                  (3, 2927, 2927, 16, 8, 32, 1), (6, 384, 384, 32, 32, 32, 1), (2, 772, 772, 4, 2, 128, 1)):
+        assert one(*shape), shape
+    for shape in ((2, 2048, 2048, 8, 8, 64, 0), (1, 8192, 200, 2, 2, 64, 0), (1, 16384, 1024, 2, 2, 64, 0),
+                  (1, 16384, 136, 32, 32, 64, 0), (1, 4096, 300, 8, 8, 64, 0), (1, 8192, 8192, 4, 4, 64, 0),
+                  (1, 16384, 1024, 2, 2, 32, 0), (2, 29, 408, 20, 20, 128, 0), (4, 1024, 1024, 16, 16, 64, 1)):
+        assert not one(*shape), shape
