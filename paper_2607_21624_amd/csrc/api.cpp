@@ -1173,7 +1173,9 @@ int32_t tuned_tile(uint32_t op, int64_t M, int64_t K, int64_t N) {
 // {8192, 12288}, {1024, 2048} x 4096 x 4096 and 4096 x 4096 x {4096, 12288}
 // products and their transposes stand, unless the model is 12% below them (Y
 // 4096 x 3072 from 2048: 72 us on 384 workgroups of 256 x 128, 57 on 192 of
-// 256 x 256):
+// 256 x 256), 20% from n128 = 1024: there it was wrong up to 1.18 (dX 8192 x 8192
+// from 256 91 us on the orders' tile, 139 on the model's; dW 11008 x 4096 from 4096
+// 389 and 438) and right from 1.21 (Y 5696 x 5360 from 720 78 and 61):
 //   n128 >= 1024, contraction >= 2048: the 256 x 256 tiles, 8 wavefronts
 //     first when A is read along its rows, 4 first for the weight gradient's
 //     transposed A;
@@ -1236,7 +1238,7 @@ int32_t default_tile(const ProjPlan& pl) {
             break;
         }
     }
-    return first >= 0 && cost(first) <= 1.12 * cost(pick) ? first : pick;
+    return first >= 0 && cost(first) <= (fill ? 1.2 : 1.12) * cost(pick) ? first : pick;
 }
 
 }  // namespace
