@@ -61,16 +61,22 @@ def build(verbose: bool = False) -> str:
     objs = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]
     jobs = [[HIPCC, *FLAGS, "-c", "-o", o, os.path.join(CSRC, s)] for s, o in zip(SOURCES, objs)]
     fast_obj = os.path.join(OBJ, "fastcall.o")
-    jobs.append(_fastcall_compile(fast_obj))
-    workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
+    workers = max(1, min(len(jobs) + 1, int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
     with ThreadPoolExecutor(workers) as ex:
+        fast = ex.submit(_run, _fastcall_compile(fast_obj), verbose)
         list(ex.map(lambda c: _run(c, verbose), jobs))
-    tmp = LIB + ".tmp"
-    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
-    os.replace(tmp, LIB)
-    tmp = FASTCALL + ".tmp"
-    _run(_fastcall_link(fast_obj, tmp), verbose)
-    os.replace(tmp, FASTCALL)
+        tmp = LIB + ".tmp"
+        _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
+        os.replace(tmp, LIB)
+        try:  # the binding works without it: what is left of a failure is a whole libfbl.so, no stale _fastcall.so
+            fast.result()
+            tmp = FASTCALL + ".tmp"
+            _run(_fastcall_link(fast_obj, tmp), verbose)
+            os.replace(tmp, FASTCALL)
+        except Exception:
+            if os.path.exists(FASTCALL):
+                os.remove(FASTCALL)
+            raise
     return LIB
 
 

@@ -22,10 +22,15 @@
 #include <c10/hip/HIPFunctions.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cmath>
 
 #include "../../include/fbl.h"
+
+#define FBL_STR2(x) #x
+#define FBL_STR(x) FBL_STR2(x)
+#define FBL_PYTHON FBL_STR(PY_MAJOR_VERSION) "." FBL_STR(PY_MINOR_VERSION)
 
 namespace {
 
@@ -356,4 +361,13 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, kMethods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall(void) { return PyModule_Create(&kModule); }
+// built_for: the torch and Python versions, for the binding to compare before it
+// makes a call here (their headers' struct layouts are compiled in).
+PyMODINIT_FUNC PyInit__fastcall(void) {
+    PyObject* m = PyModule_Create(&kModule);
+    PyObject* v = m ? Py_BuildValue("(ss)", TORCH_VERSION, FBL_PYTHON) : nullptr;
+    if (v && PyModule_AddObject(m, "built_for", v) == 0) return m;
+    Py_XDECREF(v);
+    Py_XDECREF(m);
+    return nullptr;
+}

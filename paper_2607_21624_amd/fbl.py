@@ -182,7 +182,27 @@ LIB = _load()
 # (csrc/fastcall.cpp): each does the whole call, or nothing and returns None --
 # any argument that is not a plain one, any error -- and the Python below then
 # makes the call with every check.
-from . import _fastcall as _FAST  # noqa: E402  (needs libfbl.so's runtime loaded first)
+def _load_native():
+    """The _fastcall module, or a stand-in that handles no call.  It is compiled
+    against one torch and one Python: without it, or with one of another build, the
+    Python path makes every call (the same kernels, 10 .. 16 us of host time more)."""
+    import sys
+    import torch
+    try:
+        from . import _fastcall  # after _load: it needs libfbl.so's runtime
+        wants = (torch.__version__.split("+")[0], "%d.%d" % sys.version_info[:2])
+        if _fastcall.built_for != wants:
+            raise ImportError(f"_fastcall.so was built for torch {_fastcall.built_for[0]} and Python "
+                              f"{_fastcall.built_for[1]}, running {wants[0]} and {wants[1]}")
+        return _fastcall
+    except ImportError as e:
+        import warnings
+        warnings.warn(f"native call path unavailable, calls take the Python path: {e}", RuntimeWarning)
+        no = staticmethod(lambda *args: None)
+        return type("NoNative", (), dict.fromkeys(("attn_fwd", "attn_bwd", "attn_fwd_packed", "attn_bwd_packed", "proj"), no))
+
+
+_FAST = _load_native()
 
 
 def status_str(status: int) -> str:
