@@ -1,4 +1,5 @@
-"""Wait states around the MFMAs the kernels write as inline assembly (CPU).
+"""Wait states around the MFMAs and the LDS DMA loads the kernels write as inline
+assembly (CPU).
 
 The compiler inserts the wait states the matrix cores need around its own
 MFMAs, but treats an MFMA inside an `asm` statement as an opaque instruction.
@@ -12,6 +13,14 @@ products rely on:
 * no instruction other than a product chained on the same registers reads or
   writes the MFMA's result, or writes its C operand, in the 19 wait states
   after it (the longest 32x32 product).
+
+The DMA loads (buffer_load ... lds) are opaque to it in the same way; only the
+first of a batch carries its own wait states, the later ones rely on operands
+the first has read, so the test checks for every one that
+
+* none of its scalar operands is written by a vector instruction (a spilled
+  scalar coming back by v_readlane, v_readfirstlane) in the 5 wait states before;
+* M0, its LDS address, is not written by the instruction right before it.
 
 A wait state is one issued instruction, or N + 1 for `s_nop N`.
 """
@@ -29,6 +38,9 @@ import build as fbl_build  # noqa: E402
 BEFORE = 2
 AFTER = 19
 SOURCES = ["attn_bwd_kv.hip"]
+DMA_BEFORE = 5
+DMA_SOURCES = ["attn_streams.hip", "attn_bwd_kv.hip", "proj_gemm.hip"]
+_ASM = {}
 
 
 def _regs(tok):
@@ -100,13 +112,16 @@ class Fn:
 
 
 def _asm_for(src, tmp_path):
+    if src in _ASM:
+        return _ASM[src]
     out = tmp_path / (os.path.splitext(src)[0] + ".s")
     cmd = [fbl_build.HIPCC, *fbl_build.FLAGS, "-S", "--offload-device-only", "-o", str(out),
            os.path.join(fbl_build.CSRC, src)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         pytest.fail(r.stdout + r.stderr)
-    return out.read_text().split("\n")
+    _ASM[src] = out.read_text().split("\n")
+    return _ASM[src]
 
 
 def _functions(lines):
@@ -183,4 +198,59 @@ def test_checker_flags_planted_hazards():
 def test_inline_mfma_wait_states(src, tmp_path):
     checked, problems = _problems(_functions(_asm_for(src, tmp_path)))
     assert checked > 0, "no inline-assembly MFMA found: the test no longer covers the kv pass"
+    assert not problems, "\n".join(problems[:20])
+
+
+def _sregs(tok):
+    tok = tok.strip()
+    if tok == "m0":
+        return {"m0"}
+    m = re.match(r"s\[(\d+):(\d+)\]$", tok)
+    if m:
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.match(r"s(\d+)$", tok)
+    return {int(m.group(1))} if m else set()
+
+
+def _dma_problems(fns):
+    """(inline-assembly LDS DMA loads checked, hazards found) over the kernels `fns`."""
+    checked, problems = 0, []
+    for name, fn in fns.items():
+        for i, (mn, ops, raw, in_asm) in enumerate(fn.ins):
+            if not (in_asm and mn.startswith("buffer_load") and raw.split()[-1] == "lds"):
+                continue
+            checked += 1
+            # operands: offset, resource, scalar offset (and its modifiers)
+            reads = _sregs(ops[1]) | _sregs(ops[2].split()[0]) | {"m0"}
+            for j in fn.walk(i, DMA_BEFORE, "b"):
+                mn2, ops2, raw2, _ = fn.ins[j]
+                if mn2.startswith("v_") and ops2 and _sregs(ops2[0]) & reads:
+                    problems.append(f"{name}: '{raw2}' writes a scalar operand of '{raw}' too late")
+            for j in fn.preds[i]:
+                mn2, ops2, raw2, _ = fn.ins[j]
+                if ops2 and _sregs(ops2[0]) == {"m0"}:
+                    problems.append(f"{name}: '{raw2}' writes M0 right before '{raw}'")
+    return checked, sorted(set(problems))
+
+
+def test_checker_flags_planted_dma_hazards():
+    load = lambda nop: f";;#ASMSTART\n{nop}buffer_load_dwordx4 v1, s[4:7], s9 offen lds\n;;#ASMEND"
+    n, p = _dma_problems(_snippet("s_mov_b32 m0, s3\n" + load("s_nop 0\n")))
+    assert n == 1 and p == []
+    n, p = _dma_problems(_snippet("s_mov_b32 m0, s3\n" + load("")))
+    assert n == 1 and len(p) == 1 and "M0" in p[0]
+    for reg in ("s9", "s5", "m0"):
+        n, p = _dma_problems(_snippet(f"v_readlane_b32 {reg}, v40, 3\ns_nop 1\n" + load("s_nop 0\n")))
+        assert n == 1 and len(p) == 1, reg
+        n, p = _dma_problems(_snippet(f"v_readlane_b32 {reg}, v40, 3\n" + load("s_nop 4\n\ts_nop 0\n")))
+        assert n == 1 and p == [], reg
+    n, p = _dma_problems(_snippet("v_readlane_b32 s8, v40, 3\n" + load("s_nop 0\n")))  # not an operand
+    assert n == 1 and p == []
+
+
+@pytest.mark.skipif(not os.path.exists(fbl_build.HIPCC), reason="hipcc not installed")
+@pytest.mark.parametrize("src", DMA_SOURCES)
+def test_inline_dma_wait_states(src, tmp_path):
+    checked, problems = _dma_problems(_functions(_asm_for(src, tmp_path)))
+    assert checked > 0, "no inline-assembly DMA load found: the test no longer covers these kernels"
     assert not problems, "\n".join(problems[:20])
