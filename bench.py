@@ -89,7 +89,7 @@ def design_bytes(w, es: int, kv_len=None) -> dict:
     return {"attn_bwd_stats": stats, "attn_bwd_kv": stats + ds, "attn_bwd_dq": ds}
 
 
-KERNEL_SOURCES = ("attn_streams.hip", "attn_fwd_bf16.hip", "attn_bwd.hip", "attn_bwd_kv.hip", "attn_bwd_q.hip",
+KERNEL_SOURCES = ("attn_streams.hip", "attn_rows_f32.hip", "attn_fwd_bf16.hip", "attn_bwd.hip", "attn_bwd_kv.hip", "attn_bwd_q.hip",
                   "attn_bwd_dq.hip", "attn_tiles.hpp", "stage.hpp", "cdna4.hpp", "tokmap.hpp")
 
 

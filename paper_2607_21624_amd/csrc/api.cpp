@@ -146,8 +146,10 @@ hipError_t dispatch_fwd(int32_t dtype, int D, int tile, const fbl::FwdArgs& a, h
     }
     switch (D) {
         case 32: return fbl::launch_attn_fwd_streams<float, 32>(a, s);
-        case 64: return fbl::launch_attn_fwd_streams<float, 64>(a, s);
-        default: return fbl::launch_attn_fwd_streams<float, 128>(a, s);
+        case 64: return fbl::f32_rows_fwd(a, 64) ? fbl::launch_attn_fwd_rows_f32<64>(a, s)
+                                                : fbl::launch_attn_fwd_streams<float, 64>(a, s);
+        default: return fbl::f32_rows_fwd(a, 128) ? fbl::launch_attn_fwd_rows_f32<128>(a, s)
+                                                 : fbl::launch_attn_fwd_streams<float, 128>(a, s);
     }
 }
 

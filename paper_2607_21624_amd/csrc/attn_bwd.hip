@@ -13,7 +13,7 @@
 //   attn_bwd_stats  per query row: LSE*log2(e) (+inf for an empty row) and D.
 //   attn_bwd_fused  the whole backward in one launch, up to 128 keys.
 // The kv and dQ passes are attn_bwd_kv.hip, attn_bwd_dq.hip and attn_bwd_q.hip
-// (bf16) and attn_f32.hip (fp32).  No atomics: fp32 atomics run at ~1.3 TB/s on
+// (bf16) and attn_streams.hip and attn_rows_f32.hip (fp32).  No atomics: fp32 atomics run at ~1.3 TB/s on
 // this part, far slower than the products they would save; every output is
 // written once.
 #include <type_traits>
@@ -529,7 +529,8 @@ hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream
             const hipError_t ek = launch_attn_bwd_kv_bf16<D>(a, a.kv_tile, stream);
             if (ek != hipSuccess) return ek;
         } else {
-            const hipError_t ek = launch_attn_bwd_kv_f32<D>(a, stream);
+            const hipError_t ek = D == 128 && f32_rows_kv(a) ? launch_attn_bwd_kv_rows_f32(a, stream)
+                                                              : launch_attn_bwd_kv_f32<D>(a, stream);
             if (ek != hipSuccess) return ek;
         }
     }
@@ -539,7 +540,8 @@ hipError_t launch_attn_bwd(const BwdArgs& a, unsigned phases, hipStream_t stream
                 a.ds ? launch_attn_bwd_dq_bf16<D>(a, a.dq_tile, stream) : launch_attn_bwd_q_bf16<D>(a, stream);
             if (eq != hipSuccess) return eq;
         } else {
-            const hipError_t eq = launch_attn_bwd_q_f32<D>(a, stream);
+            const hipError_t eq = D == 128 && f32_rows_q(a) ? launch_attn_bwd_q_rows_f32(a, stream)
+                                                            : launch_attn_bwd_q_f32<D>(a, stream);
             if (eq != hipSuccess) return eq;
         }
     }

@@ -60,6 +60,16 @@ hipError_t launch_attn_bwd_kv_f32(const BwdArgs& a, hipStream_t stream);
 template <int D>
 hipError_t launch_attn_bwd_q_f32(const BwdArgs& a, hipStream_t stream);
 
+// fp32 passes in 128-row workgroups for short walks (attn_rows_f32.hip), the forward at
+// d = 64 and 128 and the backward's passes at d = 128, and whether they are the faster ones.
+bool f32_rows_fwd(const FwdArgs& a, int D);
+bool f32_rows_kv(const BwdArgs& a);
+bool f32_rows_q(const BwdArgs& a);
+template <int D>
+hipError_t launch_attn_fwd_rows_f32(const FwdArgs& a, hipStream_t stream);
+hipError_t launch_attn_bwd_kv_rows_f32(const BwdArgs& a, hipStream_t stream);
+hipError_t launch_attn_bwd_q_rows_f32(const BwdArgs& a, hipStream_t stream);
+
 // Key/value-major backward pass for bf16 storage (software-pipelined kernel)
 // with kv tile `tile` of kAttnTiles (its split is a.kv_split).
 template <int D>
