@@ -363,10 +363,13 @@ fbl_status fbl_attn_candidates(uint32_t pass, const fbl_layout* lq, const fbl_la
 /*
  * The R-Tile choice of section 4.2 for one shape, the per-shape lookup the
  * paper's runtime makes (section 5.5): the ids FBL_ATTN_TILE_AUTO resolves to
- * for (lq, lk, mask kind): tiles[0]
- * forward, tiles[1] kv pass, tiles[2] dQ pass -- the measured choice of
- * fbl_attn_tune for this shape when the process holds one, else the first
- * candidate in a preference order measured on MI355X.  Host only.
+ * for (lq, lk, mask kind) where a pass runs a tile: tiles[0] forward, tiles[1]
+ * kv pass, tiles[2] dQ pass -- the measured choice of fbl_attn_tune for this
+ * shape when the process holds one, else the first candidate in a preference
+ * order measured on MI355X.  A small forward that no tuning has measured runs a
+ * kernel of 32 queries per workgroup instead (fbl_attn_fwd), and a one-launch
+ * backward (fbl_attn_bwd_launches gives 1) neither tile; the ids are then the
+ * ones an explicit choice would start from.  Host only.
  */
 fbl_status fbl_attn_auto_tiles(const fbl_layout* lq, const fbl_layout* lk, uint32_t mask_kind, int32_t* tiles);
 
@@ -419,6 +422,10 @@ fbl_status fbl_attn_bwd_tiled(uint32_t phases, const fbl_layout* lq, const void*
  * the chosen tiles.  bf16 only (FBL_ERR_DTYPE); FBL_ERR_ARG for an unknown
  * objective or reps out of range; otherwise the statuses of fbl_attn_fwd and
  * fbl_attn_bwd.
+ * It chooses among tiles.  Small calls, which untuned run the 32-row kernels and
+ * from 136 keys the one-launch backward (fbl_attn_fwd, fbl_attn_bwd), run tiles
+ * once tuned and are then usually slower: tune the shapes whose untuned calls run
+ * tiles.  fbl_attn_tune_reset brings the untuned choice back.
  */
 fbl_status fbl_attn_tune(const fbl_layout* lq, const void* q, const fbl_layout* lk, const void* k,
                          const fbl_layout* lv, const void* v, const fbl_layout* lo, void* o, float* lse,
@@ -556,6 +563,11 @@ fbl_status fbl_proj_candidates(uint32_t op, int64_t M, int64_t K, int64_t N, int
  * until the timed launches finish.  On return c holds the product computed
  * with the chosen tile.  Same checks as fbl_proj; FBL_ERR_ARG for an unknown
  * objective or reps out of range, FBL_ERR_UNSUPPORTED with no candidate.
+ * It chooses among the candidates.  The untuned choice may lie outside them, for
+ * small outputs and deep contractions, and be faster than the best of them (Y 256 x
+ * 1024 from 4096: 9.6 against 22 us): where fbl_proj_auto_tile names a tile that
+ * is no candidate, leave the shape untuned.  fbl_proj_tune_reset brings the
+ * untuned choice back.
  */
 #define FBL_TUNE_TIME 0u
 #define FBL_TUNE_GFLOPS_X_MEMEFF 1u

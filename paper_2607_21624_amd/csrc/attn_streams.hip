@@ -1,6 +1,7 @@
 // attn_streams.hip -- attention forward and backward in 32-row workgroups on
-// token-major tensors, gfx950: every fp32 call, and the bf16 calls too small for
-// the larger tiles of attn_fwd_bf16.hip, attn_bwd_kv.hip and attn_bwd_dq.hip.
+// token-major tensors, gfx950: the fp32 calls (but for short walks of many rows,
+// attn_rows_f32.hip), and the bf16 calls too small for the larger tiles of
+// attn_fwd_bf16.hip, attn_bwd_kv.hip and attn_bwd_dq.hip.
 //
 // Kernels of one shape: attn_fwd_streams (O, LSE), a kv pass (dK, dV) and a q
 // pass (dQ, recomputing S and dP).  attn_bwd_streams runs both passes as one
@@ -518,7 +519,10 @@ FBL_DEV void kv_pass(const BwdArgs& a, int id, unsigned char* kv_smem) {
         asm volatile("" : "+s"(own));  // (added at each use: no second set of addresses in registers)
         // S = Q K_w^T and dP = dO V_w^T: lane <-> key, in-lane query acc_row
         f32x16 s = f32x16{}, dp = f32x16{};
-        wait_tile<C::LOADS>();  // dO and the statistics have landed; Q may be in flight
+        // dO and the statistics have landed; Q may be in flight.  (INLINE, bf16: until the second
+        // dP product only.  The O rows and the LSE are plain loads, and the compiler, which does
+        // not count the tiles' loads behind them, waits there for all.)
+        wait_tile<C::LOADS>();
         float dsum = 0.f;
         const bool q_ok = q0 + c32 < S;
         const T* optr = static_cast<const T*>(a.o) + a.mo.head_base(b, head_of(i)) + (int64_t)min(q0 + c32, S - 1) * a.mo.ss + 8 * g;

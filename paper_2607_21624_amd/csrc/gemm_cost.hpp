@@ -14,11 +14,12 @@
 // (default_tile in api.cpp) is 2.7% slower than the best of the 21 in the
 // geometric mean and within 7% on 9 of 10 products; the preference orders alone
 // were 24% slower, within 70% on 9 of 10.
-// (The loads have since been spread over a step's products, proj_gemm.hip: on 130
-// other shapes the pick is 5.9% from the best, 4.7 .. 5.4% with constants fitted
-// again -- inside what two timings of such a sweep differ by, so they stay.  Nor
-// were the steps of tiles 11, 12 and 17 .. 20, forward and weight gradient, scaled by
-// what a swizzle without bank conflicts for 256-column tiles gave, 0.98 .. 0.85.)
+// (The loads have since been spread over a step's products, proj_gemm.hip: on 240
+// other shapes, 720 products, the pick is 4.8% from the best; constants fitted
+// again on 130 of them gained 0.5 .. 1.2% there, inside what two timings of such a
+// sweep differ by, so they stay.  Nor were the steps of tiles 11, 12 and 17 .. 20,
+// forward and weight gradient, scaled by what a swizzle without bank conflicts for
+// 256-column tiles gave, 0.98 .. 0.85.)
 #pragma once
 
 #include "gemm_tiles.hpp"

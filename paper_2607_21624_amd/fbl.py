@@ -503,7 +503,8 @@ def attn_candidates(pass_: int, lq: Layout, lk: Layout):
 
 
 def attn_auto_tiles(lq: Layout, lk: Layout, mask_kind: int):
-    """(forward, kv, dQ) tile ids FBL_ATTN_TILE_AUTO resolves to."""
+    """(forward, kv, dQ) tile ids FBL_ATTN_TILE_AUTO resolves to, where a pass
+    runs a tile (small untuned calls and one-launch backwards run none)."""
     t = (ctypes.c_int32 * 3)()
     _check(LIB.fbl_attn_auto_tiles(ctypes.byref(lq), ctypes.byref(lk), mask_kind, t), "fbl_attn_auto_tiles")
     return tuple(t)
@@ -524,7 +525,8 @@ def attn_tune(q, k, v, do, Hq: int, Hkv: int, scale: Optional[float] = None, cau
               reps: int = 10, stream=None):
     """Measured tile selection for this attention shape (fbl_attn_tune).  Returns
     ((fwd, kv, dq) chosen ids, {id: average ms}, outputs (o, lse, dq, dk, dv)
-    computed with the chosen tiles)."""
+    computed with the chosen tiles).  Among tiles only: a small shape, whose
+    untuned calls run other kernels, is usually faster left untuned."""
     import torch
     _check_kv_len(kv_len, q.shape[0], "attn_tune")
     _check_device("attn_tune", stream, q=q, k=k, v=v, do=do, kv_len=kv_len, o=o, lse=lse, dq=dq, dk=dk, dv=dv,
@@ -750,7 +752,8 @@ def proj_candidates(op: int, M: int, K: int, N: int):
 def proj_tune(op: int, a, b, out, objective: int = FBL_TUNE_TIME, reps: int = 10, stream=None):
     """Measured tile selection for one product (fbl_proj_tune).  Returns
     (chosen id, {id: average ms} over the candidates); `out` then holds the
-    product computed with the chosen tile."""
+    product computed with the chosen tile.  Where proj_auto_tile is no candidate,
+    the untuned choice may be the faster one."""
     _check_device("proj_tune", stream, a=a, b=b, out=out)
     M, K, N, _, lda, ldb = _proj_shape(op, a, b, out)
     _, _, ldc = _rows(out, "out")
