@@ -77,6 +77,8 @@ def algorithmic_bytes(w, es: int, kv_len=None) -> dict:
             "attn_bwd_dq": nk + nq,                         # read K, write dQ
             "attn_bwd_q": nk + nq,                          # (fp32: the recomputing dQ pass, same split)
             "attn_bwd_fused": 4 * nq + 4 * nk + lse,        # one launch: read Q O dO LSE K V, write dQ dK dV
+            "attn_bwd_streams": 4 * nq + 4 * nk + lse,      # (the same in 32-row workgroups)
+            "attn_bwd": 4 * nq + 4 * nk + lse,              # (either, without a kernel list)
             "total": (2 * nq + 2 * nk + lse) + (3 * nq + 2 * nk + lse + nq + 2 * nk)}
 
 
@@ -446,14 +448,15 @@ def main():
         tiles = [int(x) for x in args.tiles.split(",")]
     lq_, lk_ = fbl.layout_of(q, w.Hq), fbl.layout_of(k, w.Hkv)
     qname = "attn_bwd_dq" if w.dtype == "bf16" else "attn_bwd_q"
-    # the backward as the library runs it: one launch up to 128 keys with automatic
-    # tiles, else its three phases, each bracketed by events of its own
-    fused = fbl.attn_bwd_launches(lq_, lk_, int(w.mask), ws.numel(), kv_tile=tiles[1], dq_tile=tiles[2]) == 1
-    if fused:
-        bwd_phases = [("attn_bwd_fused", fbl.FBL_BWD_ALL)]
-    else:
-        bwd_phases = [("attn_bwd_stats", fbl.FBL_BWD_PREP), ("attn_bwd_kv", fbl.FBL_BWD_KV), (qname, fbl.FBL_BWD_Q)]
-    n_ev = 2 + len(bwd_phases)
+
+    def plan_bwd():
+        # the backward as the library runs it: one launch where it chooses that (which of the
+        # two kernels, the kernel list says), else its three phases, each bracketed by events
+        # of its own
+        if fbl.attn_bwd_launches(lq_, lk_, int(w.mask), ws.numel(), kv_tile=tiles[1], dq_tile=tiles[2]) == 1:
+            return [("attn_bwd", fbl.FBL_BWD_ALL)]
+        return [("attn_bwd_stats", fbl.FBL_BWD_PREP), ("attn_bwd_kv", fbl.FBL_BWD_KV), (qname, fbl.FBL_BWD_Q)]
+    bwd_phases = plan_bwd()
 
     def bwd(phases):
         fbl.attn_bwd(q, k, v, o, do, lse, w.Hq, w.Hkv, scale, causal, kv_len, dq=dq, dk=dk, dv=dv, workspace=ws,
@@ -485,16 +488,23 @@ def main():
                                      dv=dv, workspace=ws, reps=5)
         torch.cuda.synchronize()
         tune = {"chosen": list(best), "ms": {str(t): round(x, 4) for t, x in tms.items()}}
+        bwd_phases = plan_bwd()  # (a tuned shape may take three launches where the untuned one took one)
+    fused = len(bwd_phases) == 1
+    n_ev = 2 + len(bwd_phases)
     auto = fbl.attn_auto_tiles(lq_, lk_, int(w.mask)) if w.dtype == "bf16" else None
     run_tiles = None if auto is None else [a if t == fbl.FBL_ATTN_TILE_AUTO else t for t, a in zip(tiles, auto)]
     # Algorithmic FLOPs per launch (2*d per allowed pair per matrix product):
     #   attn_fwd        QK^T, PV                                    4*d
     #   attn_bwd_kv     QK^T recompute, dO V^T, P^T dO, dS^T Q      8*d
     #   attn_bwd_dq     dS K from the dS the kv pass stored         2*d
-    #   attn_bwd_fused  the kv products and dS K in one launch     10*d
-    #   (fp32 storage has no stored-dS path: attn_bwd_q recomputes QK^T and dO V^T, 6*d executed)
-    alg = {"attn_fwd": 4, "attn_bwd_kv": 8, "attn_bwd_dq": 2, "attn_bwd_q": 2, "attn_bwd_fused": 10}
-    executed = {**alg, "attn_bwd_q": 6}
+    #   attn_bwd_fused, attn_bwd_streams; attn_bwd where no kernel list tells which
+    #                   the kv products and dS K in one launch     10*d
+    #   (fp32 storage has no stored-dS path: attn_bwd_q recomputes QK^T and dO V^T, 6*d
+    #   executed; so do the 32-row workgroups of one launch, 14*d)
+    alg = {"attn_fwd": 4, "attn_bwd_kv": 8, "attn_bwd_dq": 2, "attn_bwd_q": 2, "attn_bwd_fused": 10,
+           "attn_bwd_streams": 10, "attn_bwd": 10}
+    executed = {**alg, "attn_bwd_q": 6, "attn_bwd_streams": 14}
+    del executed["attn_bwd"]
     # The dominant launch (most algorithmic FLOPs) is timed inside the timed
     # steps with events just around it (for the roofline): each event recorded
     # between two launches adds a gap to the step.  Every launch is timed in as
@@ -554,13 +564,19 @@ def main():
         torch.cuda.synchronize()
         ms_per_step = start.elapsed_time(stop) / args.steps
 
+    kernels = None if args.no_kernel_list else dispatched_kernels(step)
+    for one in ("attn_bwd_fused", "attn_bwd_streams"):
+        if fused and any(one in n for n in kernels or []):
+            k_ms[one] = k_ms.pop("attn_bwd")
+            dom = one if dom == "attn_bwd" else dom
+
     pairs = allowed_pairs(w, inp["kv_len"])
     flops = 14 * w.d * pairs
     tflops = flops / (ms_per_step * 1e-3) / 1e12
     peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_F32_TFLOPS
     per_kernel = {n: (t, alg[n]) for n, t in k_ms.items() if n in alg}
     ktf = {n: a * w.d * pairs / (t * 1e-3) / 1e12 for n, (t, a) in per_kernel.items()}
-    ktf_exec = {n: executed[n] * w.d * pairs / (per_kernel[n][0] * 1e-3) / 1e12 for n in per_kernel}
+    ktf_exec = {n: executed[n] * w.d * pairs / (per_kernel[n][0] * 1e-3) / 1e12 for n in per_kernel if n in executed}
     a_dom = alg[dom]
     t_dom = t_dom_timed
     es = 2 if w.dtype == "bf16" else 4
@@ -591,7 +607,6 @@ def main():
     stat = lambda x: {"median": round(float(np.median(x)), 4), "min": round(float(np.min(x)), 4),
                       "max": round(float(np.max(x)), 4)}
 
-    kernels = None if args.no_kernel_list else dispatched_kernels(step)
     foreign = None
     if kernels is not None:
         foreign = [n for n in kernels if not any(t in n for t in ("attn_fwd", "attn_bwd"))]
@@ -637,6 +652,8 @@ def main():
         "algorithmic_gflop": round(flops / 1e9, 3),
         "algorithmic_bytes": alg_bytes["total"],
         "roofline": roofline,
+        # (the ids automatic tiles resolve to; kernels of 32-row workgroups, and the one-launch
+        # backward, run none of them)
         "attn_tiles": run_tiles,
         "tune": tune,
         "cpu_baseline": cpu,
