@@ -1175,9 +1175,15 @@ int32_t tuned_tile(uint32_t op, int64_t M, int64_t K, int64_t N) {
 // {8192, 12288}, {1024, 2048} x 4096 x 4096 and 4096 x 4096 x {4096, 12288}
 // products and their transposes stand, unless the model is 12% below them (Y
 // 4096 x 3072 from 2048: 72 us on 384 workgroups of 256 x 128, 57 on 192 of
-// 256 x 256), 20% from n128 = 1024: there it was wrong up to 1.18 (dX 8192 x 8192
-// from 256 91 us on the orders' tile, 139 on the model's; dW 11008 x 4096 from 4096
-// 389 and 438) and right from 1.21 (Y 5696 x 5360 from 720 78 and 61):
+// 256 x 256).  From n128 = 1024, of 200 products (us, orders' tile and model's):
+//   a smaller tile than 256 x 256 takes 20%: below that it was wrong (dW 11008 x 4096
+//     from 4096 389 and 438, dX 8528 x 2560 from 11008 540 and 620);
+//   the 256 x 256 tile is right from 12% (dX 12288 x 2560 from 1536 133 and 98, Y 12288
+//     x 2560 from 512 59 and 48) but where rows of a power of two of 16 KB and more are
+//     stored by several rounds of workgroups, whatever the model says of it (dX 8192 x
+//     8192 from 384 104 and 152, from 1024 187 and 217; Y 2048 x 16384 from 896 80 and
+//     120; one round, Y 2048 x 8192 from 896, 39 and 35; 12288 columns, dX 4096 x
+//     12288 from 384, 71 and 62):
 //   n128 >= 1024, contraction >= 2048: the 256 x 256 tiles, 8 wavefronts
 //     first when A is read along its rows, 4 first for the weight gradient's
 //     transposed A;
@@ -1240,7 +1246,13 @@ int32_t default_tile(const ProjPlan& pl) {
             break;
         }
     }
-    return first >= 0 && cost(first) <= (fill ? 1.2 : 1.12) * cost(pick) ? first : pick;
+    if (first < 0) return pick;
+    const fbl::GemmTile& g = fbl::kGemmTiles[pick];
+    const bool largest = g.bm == 256 && g.bn == 256;
+    if (fill && largest && pl.ocols >= 8192 && (pl.ocols & (pl.ocols - 1)) == 0 &&
+        ((pl.orows + 255) / 256) * (pl.ocols / 256) > 256)
+        return first;
+    return cost(first) <= (fill && !largest ? 1.2 : 1.12) * cost(pick) ? first : pick;
 }
 
 }  // namespace
