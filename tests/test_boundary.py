@@ -769,3 +769,40 @@ def test_proj_auto_tile_large_outputs():
     assert A(DW, 512, 2048, 8192) == 19 and A(FWD, 2048, 896, 8192) == 19
     assert A(DX, 4096, 12288, 384) == 19 and A(DX, 12288, 2560, 1536) == 19
     assert A(FWD, 12288, 512, 2560) == 19 and A(FWD, 5696, 720, 5360) == 19
+
+
+@pytest.mark.parametrize("case", ["absent", "other torch", "unloadable"])
+def test_binding_without_the_native_call_path(case, tmp_path):
+    """The package imports and its Python path makes the calls where _fastcall.so is
+    missing, was built for another torch, or does not load; a warning says so."""
+    import shutil
+    import subprocess
+    import sys
+    src = os.path.dirname(F.LIB_PATH)
+    pkg = tmp_path / os.path.basename(src)
+    pkg.mkdir()
+    for f in os.listdir(src):
+        if f.endswith((".py", ".so")) and not (case == "absent" and f == "_fastcall.so"):
+            shutil.copy(os.path.join(src, f), pkg / f)
+    if case == "unloadable":
+        (pkg / "_fastcall.so").write_bytes(b"not a library")
+    code = f"""
+import warnings, torch
+if {case == 'other torch'}:
+    torch.__version__ = "0.0.0+other"
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    import {pkg.name} as fbl
+assert any("native call path unavailable" in str(x.message) for x in w), [str(x.message) for x in w]
+q = torch.zeros(1, 64, 128)
+for call in (lambda: fbl.attn_fwd(q, q, q, 2, 2), lambda: fbl.attn_bwd(q, q, q, q, q, None, 2, 2),
+             lambda: fbl.proj(0, q[0], q[0])):
+    try:
+        call()
+        raise SystemExit("a CPU tensor was taken")
+    except fbl.FblError as e:
+        assert "not on a GPU" in str(e)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True,
+                       env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert r.returncode == 0, r.stdout + r.stderr
