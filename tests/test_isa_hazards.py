@@ -39,7 +39,7 @@ BEFORE = 2
 AFTER = 19
 SOURCES = ["attn_bwd_kv.hip"]
 DMA_BEFORE = 5
-DMA_SOURCES = ["attn_streams.hip", "attn_bwd_kv.hip", "proj_gemm.hip"]
+DMA_SOURCES = ["attn_streams.hip", "attn_rows_f32.hip", "attn_bwd_kv.hip", "proj_gemm.hip"]
 _ASM = {}
 
 
