@@ -267,15 +267,6 @@ FBL_DEV void col_product(f32x16* acc, const StreamLane<T, D>& la, uint32_t off, 
     }
 }
 
-// v_mul_legacy_f32: 0 times anything is 0.  (The compiler has no builtin of this name; the
-// intrinsic lets it place the wait states.)
-extern "C" __device__ float mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
-
-// dS = p (dP - D), and 0 where p is: a masked key's V row may hold anything finite, and its
-// dP then be inf or nan.  A second select instead of the product costs registers (B8 S128
-// H12 d64 bf16 8.8 -> 9.3 us); this one costs nothing at d = 32 and 64, 3% at 128.
-FBL_DEV float masked_ds(float p, float x) { return mul_legacy(p, x); }
-
 // Partial results through LDS: slot w holds one wavefront's 32 x D result as
 // [quad][lane] x 16 bytes.
 template <typename T, int D>

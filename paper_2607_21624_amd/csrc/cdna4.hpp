@@ -107,6 +107,16 @@ FBL_DEV float other_half(float x) {
 
 FBL_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// v_mul_legacy_f32: 0 times anything is 0.  (The compiler has no builtin of this name; the
+// intrinsic lets it place the wait states.)
+extern "C" __device__ float mul_legacy(float, float) __asm("llvm.amdgcn.fmul.legacy");
+
+// dS = p (dP - D), and 0 where p is: a masked key's V row may hold anything finite, and its
+// dP then be inf or nan.  A second select instead of the product costs registers (one-launch
+// backwards, us: 32-row workgroups B8 S128 H12 d64 bf16 8.8 -> 9.3, whole pairs B64 S64 H16
+// d32 27.2 -> 28.7).
+FBL_DEV float masked_ds(float p, float x) { return mul_legacy(p, x); }
+
 // ------------------------------------------------------- global <-> LDS copies
 // 16-byte global load; rows outside [0, nrows) read as zeros.
 FBL_DEV uint4 load16(const void* p) { return *reinterpret_cast<const uint4*>(p); }

@@ -63,3 +63,38 @@ def test_fused_backward(name, B, Sq, Skv, Hq, Hkv, d, dt, mask):
         errs, bad = compare(got, ref, dt)
         note(f"{label} rel errs {errs}")
         assert not bad, f"{name} {label}: {bad} (tol {TOL[dt]})"
+
+
+@pytest.mark.parametrize("dt,d", [("bfloat16", 32), ("bfloat16", 64), ("bfloat16", 128), ("float32", 32), ("float32", 64)])
+def test_masked_rows_may_hold_anything_finite(dt, d):
+    """Key padding over values whose scores and dP overflow to inf and nan: the results
+    are those of zeros in their place, and the masked keys' gradients are zeros, also
+    where dO is nan."""
+    import bench
+    import torch
+    import paper_2607_21624_amd as fbl
+    dt = getattr(torch, dt)
+    B, S, H = 16, 100, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, k, v, do = (torch.randn(B, S, H * d, generator=g, device="cuda").to(dt) for _ in range(4))
+    lens = torch.randint(1, S + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lens[:3] = torch.tensor([0, 31, 64])
+    pad = torch.arange(S, device="cuda")[None, :] >= lens[:, None]
+    note(f"masked rows {dt} d={d}")
+
+    def run(k, v, do):
+        o, lse = fbl.attn_fwd(q, k, v, H, H, kv_len=lens)
+        r = (o, lse) + tuple(fbl.attn_bwd(q, k, v, o, do, lse, H, H, kv_len=lens))
+        torch.cuda.synchronize()
+        return r
+
+    ran = bench.dispatched_kernels(lambda: run(k, v, do))
+    assert ran is None or any("attn_bwd_fused" in n for n in ran), ran
+    fill = lambda t, x: torch.where(pad[:, :, None], torch.tensor(x, dtype=dt, device="cuda"), t)
+    for a, b in zip(run(fill(k, 1e30), fill(v, 3e38), do), run(fill(k, 0.0), fill(v, 0.0), do)):
+        assert not a.isnan().any() and torch.equal(a, b)  # (LSE is -inf in the batch without keys)
+    bad = do.clone()
+    bad[:, 7] = float("nan")
+    for t in run(k, v, bad)[3:]:
+        assert (t[pad] == 0).all()
