@@ -43,3 +43,45 @@ def test_rows_kernels(B, Sq, Skv, Hq, Hkv, d, mask, kernels):
     if ran is not None:
         for k in kernels:
             assert any(f"_{k}_rows_f32" in n for n in ran), (k, ran)
+
+
+@pytest.mark.parametrize("Sq,Skv,d", [(128, 128, 64), (128, 128, 128), (500, 50, 128)])
+def test_rows_kernels_strides_and_masked_rows(Sq, Skv, d):
+    """Views of packed buffers give the contiguous tensors' results bit for bit, and
+    so do zeros in the place of padded keys whose scores and dP overflow; the padded
+    keys' gradients are zeros, also where dO is nan."""
+    import torch
+    import paper_2607_21624_amd as fbl
+    B, H = 16, 16
+    W = H * d
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Sq + d)
+    qd = torch.randn(B, Sq, 2 * W, generator=g, device="cuda")
+    kv = torch.randn(B, Skv, 2 * W, generator=g, device="cuda")
+    lens = torch.randint(1, Skv + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lens[0] = 0
+    pad = torch.arange(Skv, device="cuda")[None, :] >= lens[:, None]
+    note(f"rows, packed views Sq={Sq} Skv={Skv} d={d}")
+
+    def run(q, k, v, do):
+        out = torch.full_like(q, float("nan"))
+        o, lse = fbl.attn_fwd(q, k, v, H, H, kv_len=lens, out=out)
+        gr = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+        fbl.attn_bwd(q, k, v, o, do, lse, H, H, kv_len=lens, dq=gr[0], dk=gr[1], dv=gr[2])
+        torch.cuda.synchronize()
+        return [o, lse] + gr
+
+    views = [qd[:, :, :W], kv[:, :, :W], kv[:, :, W:], qd[:, :, W:]]
+    assert not any(t.is_contiguous() for t in views)
+    want = run(*(t.contiguous() for t in views))
+    for a, b in zip(run(*views), want):
+        assert not a.isnan().any() and torch.equal(a, b)  # (LSE is -inf in the batch without keys)
+    big, zero = kv.clone(), kv.clone()
+    big[:, :, :W][pad], big[:, :, W:][pad], zero[pad] = 1e30, 3e38, 0.0
+    want = run(views[0], zero[:, :, :W], zero[:, :, W:], views[3])
+    for a, b in zip(run(views[0], big[:, :, :W], big[:, :, W:], views[3]), want):
+        assert not a.isnan().any() and torch.equal(a, b)  # (LSE is -inf in the batch without keys)
+    views[3] = views[3].clone()
+    views[3][:, 7] = float("nan")
+    for t in run(*views)[3:]:
+        assert (t[pad] == 0).all()
